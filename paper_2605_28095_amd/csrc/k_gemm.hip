@@ -50,13 +50,6 @@ __host__ __device__ inline int round_up(int a, int b) { return (a + b - 1) / b *
 // column group are adjacent, so the waves of a grid that all stand at the same
 // k-tile read one contiguous stretch of the weights (spread over every HBM
 // channel) rather than one 8 KB piece in each of NG regions a group apart.
-__device__ __forceinline__ void packed_coords(int64_t chunk, int NG, int& lane, int& nf, int& kb, int& ng) {
-  lane = (int)(chunk % 64);
-  nf = (int)((chunk / 64) % 2);
-  const int ks = (int)((chunk / 128) % 4);
-  ng = (int)((chunk / 512) % NG);
-  kb = (int)(chunk / (512 * (int64_t)NG)) * 4 + ks;
-}
 
 // Rows of the matrix to pack, taken from up to three sources stacked in
 // order (the QKV projection packs W_q, W_k, W_v as one matrix).
@@ -65,44 +58,68 @@ struct PackRows {
   int n[3];  // rows from each source; the packed matrix has n[0] + n[1] + n[2]
 };
 
-// W [N, K] (the stacked sources) -> packed as above, zero padded.
-__global__ void k_pack_linear(PackRows src, int N, int K, int KB, int NG, uint16_t* __restrict__ out) {
-  const int64_t chunk = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;  // one 8-element chunk
-  const int64_t total = (int64_t)NG * KB * 2 * 64;
-  if (chunk >= total) return;
-  int lane, nf, kb, ng;
-  packed_coords(chunk, NG, lane, nf, kb, ng);
-  int n = ng * 64 + nf * 32 + (lane % 32);
-  const bool in_rows = n < N;
-  int seg = 0;
-  while (seg < 2 && n >= src.n[seg]) n -= src.n[seg++];
-  const uint16_t* w = src.w[seg];
-  const int k0 = kb * 16 + (lane / 32) * 8;
-  uint16_t v[8];
+// W (the stacked sources, [N, K]) -> packed as above, zero padded. With GATE_UP
+// the sources are gate and up [N, K] and column group j takes {gate rows 32j ..
+// 32j + 31, up rows 32j .. 32j + 31}. A workgroup turns one k-tile of one
+// column group: 64 rows x 128 bytes in, one contiguous 8 KB piece out, so both
+// sides move whole cache lines and the turn into fragment order happens in LDS.
+// HBM-bound: a 5120-wide layer (0.98 GB) packs at 5.46 TB/s of read + write in
+// 357 us, the rate of a plain copy; reading in fragment order (32-byte pieces
+// of 32 rows per instruction) took 960 us. Two k-tiles per workgroup 362 us,
+// four 692 us (too few workgroups in flight beside 32 KB of LDS each), cached
+// instead of streaming stores 380 us.
+// ALIGNED: K % 8 == 0 and 16-byte aligned sources, so that a chunk is one
+// 16-byte load; else a chunk is gathered by elements.
+template <bool GATE_UP, bool ALIGNED>
+__global__ void __launch_bounds__(256) k_pack(PackRows src, int N, int K, int NG, uint16_t* __restrict__ out) {
+  __shared__ u32x4_t lds[512];
+  const int ng = blockIdx.x % NG, kt = blockIdx.x / NG;
+  const int c = threadIdx.x % 8;  // chunk of the row: k step c / 2, k half c % 2
+  const int64_t k0 = (int64_t)kt * kBK + c * 8;
+  u32x4_t v[2];
 #pragma unroll
-  for (int i = 0; i < 8; i++) v[i] = (in_rows && k0 + i < K) ? w[(int64_t)n * K + k0 + i] : (uint16_t)0;
-  uint16_t* dst = out + chunk * 8;
+  for (int i = 0; i < 2; i++) {
+    const int r = threadIdx.x / 8 + i * 32;  // row of the column group; i is its column half
+    const uint16_t* w;
+    int n;
+    bool in;
+    if (GATE_UP) {
+      n = ng * 32 + r % 32;
+      in = n < N;
+      w = src.w[i];
+    } else {
+      n = ng * 64 + r;
+      in = n < N;
+      int seg = 0;
+      while (seg < 2 && n >= src.n[seg]) n -= src.n[seg++];
+      w = src.w[seg];
+    }
+    v[i] = u32x4_t{0, 0, 0, 0};
+    if (in && k0 < K) {
+      const uint16_t* p = w + (int64_t)n * K + k0;
+      if (ALIGNED) {
+        v[i] = __builtin_nontemporal_load((const u32x4_t*)p);
+      } else {
+        uint16_t e[8];
 #pragma unroll
-  for (int i = 0; i < 8; i++) dst[i] = v[i];
-}
-
-// gate, up [F, K] -> packed with n-group j = {gate rows 32j..32j+31, up rows 32j..32j+31}.
-__global__ void k_pack_gate_up(const uint16_t* __restrict__ wg, const uint16_t* __restrict__ wu, int F,
-                               int K, int KB, int NG, uint16_t* __restrict__ out) {
-  const int64_t chunk = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t total = (int64_t)NG * KB * 2 * 64;
-  if (chunk >= total) return;
-  int lane, nf, kb, ng;
-  packed_coords(chunk, NG, lane, nf, kb, ng);
-  const int f = ng * 32 + (lane % 32);
-  const int k0 = kb * 16 + (lane / 32) * 8;
-  const uint16_t* src = nf == 0 ? wg : wu;
-  uint16_t v[8];
+        for (int j = 0; j < 8; j++) e[j] = k0 + j < K ? p[j] : (uint16_t)0;
 #pragma unroll
-  for (int i = 0; i < 8; i++) v[i] = (f < F && k0 + i < K) ? src[(int64_t)f * K + k0 + i] : (uint16_t)0;
-  uint16_t* dst = out + chunk * 8;
+        for (int j = 0; j < 4; j++) v[i][j] = e[2 * j] | ((uint32_t)e[2 * j + 1] << 16);
+      }
+    }
+  }
+  // Chunk c of a half's 32 rows is one run of 32 slots; row r sits at slot
+  // (r % 32) ^ c of it, so that a row's chunks fall on different bank groups.
 #pragma unroll
-  for (int i = 0; i < 8; i++) dst[i] = v[i];
+  for (int i = 0; i < 2; i++) lds[(i * 8 + c) * 32 + ((threadIdx.x / 8) ^ c)] = v[i];
+  __syncthreads();
+  u32x4_t* dst = (u32x4_t*)out + ((int64_t)kt * NG + ng) * 512;
+#pragma unroll
+  for (int i = 0; i < 2; i++) {
+    const int p = threadIdx.x + i * 256;  // packed chunk: k step p / 128, column half, k half, row
+    const int nf = p / 64 % 2, cc = p / 128 * 2 + p / 32 % 2;
+    __builtin_nontemporal_store(lds[(nf * 8 + cc) * 32 + (p % 32 ^ cc)], dst + p);
+  }
 }
 
 // ---------------------------------------------------------------- GEMM
@@ -599,31 +616,31 @@ size_t gemm_ws_bytes(int M, int n_cols_packed, int K, int num_cus) {
   return (size_t)s * M * round_up(n_cols_packed, 64) * sizeof(float);
 }
 
-static hipError_t launch_pack_rows(const PackRows& src, int n, int k, void* packed, hipStream_t s) {
-  const int NG = round_up(n, 64) / 64, KB = round_up(k, 64) / 16;
-  const int64_t chunks = (int64_t)NG * KB * 128;
-  k_pack_linear<<<(unsigned)((chunks + 255) / 256), 256, 0, s>>>(src, n, k, KB, NG, (uint16_t*)packed);
+template <bool GATE_UP>
+static hipError_t launch_pack(const PackRows& src, int n, int k, int NG, void* packed, hipStream_t s) {
+  bool aligned = k % 8 == 0;
+  for (const uint16_t* w : src.w) aligned = aligned && (uintptr_t)w % 16 == 0;
+  const unsigned grid = (unsigned)NG * (round_up(k, 64) / kBK);
+  if (aligned) k_pack<GATE_UP, true><<<grid, 256, 0, s>>>(src, n, k, NG, (uint16_t*)packed);
+  else k_pack<GATE_UP, false><<<grid, 256, 0, s>>>(src, n, k, NG, (uint16_t*)packed);
   return hipGetLastError();
 }
 
 hipError_t launch_pack_linear(const void* w, int n, int k, void* packed, hipStream_t s) {
   PackRows src{{(const uint16_t*)w, nullptr, nullptr}, {n, 0, 0}};
-  return launch_pack_rows(src, n, k, packed, s);
+  return launch_pack<false>(src, n, k, round_up(n, 64) / 64, packed, s);
 }
 
 hipError_t launch_pack_qkv(const void* wq, const void* wk, const void* wv, int nq, int nkv, int k, void* packed,
                            hipStream_t s) {
   PackRows src{{(const uint16_t*)wq, (const uint16_t*)wk, (const uint16_t*)wv}, {nq, nkv, nkv}};
-  return launch_pack_rows(src, nq + 2 * nkv, k, packed, s);
+  const int n = nq + 2 * nkv;
+  return launch_pack<false>(src, n, k, round_up(n, 64) / 64, packed, s);
 }
 
 hipError_t launch_pack_gate_up(const void* wg, const void* wu, int f, int k, void* packed, hipStream_t s) {
-  const int F32 = round_up(f, 32);
-  const int NG = 2 * F32 / 64, KB = round_up(k, 64) / 16;
-  const int64_t chunks = (int64_t)NG * KB * 128;
-  k_pack_gate_up<<<(unsigned)((chunks + 255) / 256), 256, 0, s>>>((const uint16_t*)wg, (const uint16_t*)wu, f, k, KB,
-                                                                  NG, (uint16_t*)packed);
-  return hipGetLastError();
+  PackRows src{{(const uint16_t*)wg, (const uint16_t*)wu, nullptr}, {f, f, 0}};
+  return launch_pack<true>(src, f, k, 2 * round_up(f, 32) / 64, packed, s);
 }
 
 template <int MF, int EPI, bool P, int W = kWaves>
