@@ -27,6 +27,8 @@ struct LinearCall {
   // leave split-K partials in ws for the consumer to reduce (it must sum them
   // in split order and apply the epilogue); ignored when there is one split
   bool defer_reduce = false;
+  // the call runs beside a slot fill (a streamed step)
+  bool beside_fill = false;
 };
 
 size_t packed_bytes(int n, int k);

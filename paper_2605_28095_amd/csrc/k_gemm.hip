@@ -27,21 +27,17 @@
 //    or by the kernel that consumes the result (the RoPE/KV-append kernel for
 //    QKV, the residual + RMSNorm reduction for O and down; LinearCall's
 //    defer_reduce and norm_out select this).
+//  * k_gemm runs beside slot fills (and on unaligned activations); projections
+//    with the chip to themselves run on k_gemm_deep (k_gemm_deep.hip), the same
+//    tiles and sums with a deeper pipeline.
 //  * k_gemm_lw is the same contraction with 256-row workgroups whose weight
 //    tiles are staged once per CU in LDS (direct-to-LDS loads) and shared by
 //    both 128-row halves. It halves the weight loads per flop but needs twice
 //    the splits at a given batch; launch_linear takes it only where k_gemm
 //    would leave a quarter of the CUs idle (use_lds_weights).
-#include "common.h"
-#include "internal.h"
+#include "gemm.h"
 
 namespace sidp {
-
-constexpr int kWaves = 4;          // waves per workgroup, one column group each
-constexpr int kBK = 64;            // k per LDS stage
-constexpr int kFragElems = 512;    // 64 lanes x 8 bf16
-
-__host__ __device__ inline int round_up(int a, int b) { return (a + b - 1) / b * b; }
 
 // ---------------------------------------------------------------- packing
 
@@ -123,74 +119,6 @@ __global__ void __launch_bounds__(256) k_pack(PackRows src, int N, int K, int NG
 }
 
 // ---------------------------------------------------------------- GEMM
-
-struct GemmArgs {
-  const uint16_t* x;   // [M, K] bf16, row stride K
-  const uint16_t* w;   // packed
-  int M, K, KP;        // KP = K rounded up to 64
-  int NG;              // packed column groups (64 columns each)
-  int tiles;           // ceil(NG / waves per workgroup)
-  int splits;
-  int N;               // valid output columns (SWIGLU: F)
-  int mblocks;         // row blocks of BM rows
-  void* out;
-  const uint16_t* bias;  // EPI_BF16
-  const float* resid;    // EPI_RESID
-  float* ws;             // split-K partials [splits][M][NG*64]
-};
-
-__device__ __forceinline__ float silu_f(float g) { return g / (1.0f + __expf(-g)); }
-
-constexpr uint32_t kRsrcWord3 = 0x00020000u;  // gfx9 raw buffer: 32-bit data, bounds-checked
-constexpr uint32_t kOutOfRange = 0x80000000u;  // any offset past num_records reads as zero
-
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* p, uint32_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)bytes, (int)kRsrcWord3);
-}
-
-__device__ __forceinline__ u32x4_t buf_load16(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
-  return __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0));
-}
-
-// Writes one wave's tile: rows row0 + [0, 32 MF), the 64 packed columns of
-// group ng; acc[m][nf] holds the 32x32 block (m, nf) in the MFMA's layout
-// (register r of lane l: row 8 (r / 4) + 4 (l / 32) + r % 4, column l % 32).
-template <int MF, int EPI, bool PARTIAL>
-__device__ __forceinline__ void store_tile(const GemmArgs& a, const f32x16_t (&acc)[MF][2], int row0, int ng,
-                                           int split, int lane) {
-  const int NP = a.NG * 64;
-#pragma unroll
-  for (int m = 0; m < MF; m++) {
-#pragma unroll
-    for (int r = 0; r < 16; r++) {
-      const int row = row0 + m * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
-      if (row >= a.M) continue;
-      if (PARTIAL) {
-        float* dst = a.ws + ((int64_t)split * a.M + row) * NP + ng * 64 + (lane & 31);
-        dst[0] = acc[m][0][r];
-        dst[32] = acc[m][1][r];
-      } else if (EPI == SIDP_EPI_SWIGLU) {
-        const int f = ng * 32 + (lane & 31);
-        if (f < a.N)
-          ((uint16_t*)a.out)[(int64_t)row * a.N + f] = f2bf(silu_f(acc[m][0][r]) * acc[m][1][r]);
-      } else {
-#pragma unroll
-        for (int nf = 0; nf < 2; nf++) {
-          const int n = ng * 64 + nf * 32 + (lane & 31);
-          if (n >= a.N) continue;
-          const int64_t o = (int64_t)row * a.N + n;
-          if (EPI == SIDP_EPI_BF16) {
-            float v = acc[m][nf][r];
-            if (a.bias) v += bf2f(a.bias[n]);
-            ((uint16_t*)a.out)[o] = f2bf(v);
-          } else {
-            ((float*)a.out)[o] = a.resid ? a.resid[o] + acc[m][nf][r] : acc[m][nf][r];
-          }
-        }
-      }
-    }
-  }
-}
 
 // One workgroup: W waves (4, or 8 for wide unsplit launches). Wave wn
 // computes rows [row0, row0 + MF*32) x the 64 packed columns of group
@@ -369,9 +297,6 @@ constexpr int kLwBK = 32;                    // k per stage
 constexpr int kLwA = kLwRows * kLwBK;        // bf16 elements of a stage's activations (16 KB)
 constexpr int kLwW = 4 * 4 * kFragElems;     // 4 groups x 4 fragments (16 KB)
 
-// s_waitcnt vmcnt(0): expcnt and lgkmcnt at their no-wait maxima (7, 15)
-__device__ __forceinline__ void wait_vm0() { __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8)); }
-
 template <int EPI, bool PARTIAL>
 __global__ void __launch_bounds__(512, 1) k_gemm_lw(GemmArgs a) {
   __builtin_amdgcn_s_setprio(3);  // as k_gemm: ahead of the slot-fill waves sharing the CU
@@ -487,13 +412,13 @@ __global__ void __launch_bounds__(512, 1) k_gemm_lw(GemmArgs a) {
     load_w(sn, wn);
     if (active) mma_stage(xa, wl);
     store_x(xn);
-    wait_vm0();  // this wave's direct-to-LDS loads have landed before the barrier
+    wait_vm<0>();  // this wave's direct-to-LDS loads have landed before the barrier
     __syncthreads();
   };
   load_x(st0);
   load_w(st0, lw_w0);
   store_x(lw_a0);
-  wait_vm0();
+  wait_vm<0>();
   __syncthreads();
   int st = st0;
   for (; st + 1 < st1; st += 2) {
@@ -752,15 +677,21 @@ hipError_t launch_linear(const LinearCall& c, hipStream_t s) {
   // 8 a wide unsplit k_gemm, 0 the 4-wave k_gemm
   const GemmPlan plan = plan_linear(c.m, c.n, c.k, c.epilogue, c.num_cus);
   const int wide = plan.kernel == 1 ? -1 : plan.waves > kWaves ? plan.waves : 0;
+  // Alone on the chip the deep pipeline is the faster form of kernel 0 at every
+  // size measured; beside a slot fill the shallow one is (both sides' times in
+  // k_gemm_deep.hip). Its direct-to-LDS loads need 16-byte aligned activations.
+  const bool deep = plan.kernel == 0 && !c.beside_fill && (uintptr_t)c.x % 16 == 0;
   hipError_t e;
   if (a.splits == 1) {
-    if (c.epilogue == SIDP_EPI_BF16) e = launch_epi<SIDP_EPI_BF16, false>(a, s, wide);
+    if (deep) e = launch_gemm_deep(a, c.epilogue, plan.rows, plan.waves, s);
+    else if (c.epilogue == SIDP_EPI_BF16) e = launch_epi<SIDP_EPI_BF16, false>(a, s, wide);
     else if (c.epilogue == SIDP_EPI_RESID) e = launch_epi<SIDP_EPI_RESID, false>(a, s, wide);
     else e = launch_epi<SIDP_EPI_SWIGLU, false>(a, s, wide);
     if (e != hipSuccess || !fuse_norm) return e;
     return launch_rmsnorm((const float*)c.out, c.norm_gain, c.norm_eps, c.norm_out, a.M, a.N, s);
   }
-  e = launch_epi<SIDP_EPI_BF16, true>(a, s, wide);  // partials only; epilogue in the reduction
+  // partials only; epilogue in the reduction
+  e = deep ? launch_gemm_deep(a, c.epilogue, plan.rows, plan.waves, s) : launch_epi<SIDP_EPI_BF16, true>(a, s, wide);
   if (e != hipSuccess || c.defer_reduce) return e;
   if (fuse_norm && reduce_resid_norm_fits(a.N))
     return launch_reduce_resid_norm(a.ws, a.splits, a.M, a.NG * 64, a.N, (float*)c.out, c.norm_gain, c.norm_eps,

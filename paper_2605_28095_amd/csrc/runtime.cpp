@@ -212,6 +212,7 @@ struct sidp_handle {
   // its weights; 0: the layer waits for its whole fill before it starts
   int part_waits = 1;
   int step_batch = 0;  // rows of the decode step being issued
+  bool step_streamed = false;  // a streamed decode step is being issued: its projections run beside slot fills
   // pooling: which part of a layer is staged, and which layers this rank owns
   int pool_mode = SIDP_POOL_LAYER;
   int ranks = 0, rank = 0;          // layer l is owned (never staged) when ranks > 0 and l % ranks == rank
@@ -533,6 +534,7 @@ static LinearCall linear_call(const sidp_handle* h, const void* x, int m, int k,
   c.ws = h->ws;
   c.ws_bytes = h->ws_bytes;
   c.num_cus = h->num_cus;
+  c.beside_fill = h->step_streamed;
   return c;
 }
 
@@ -778,6 +780,7 @@ int sidp_decode_step(sidp_handle* h, float* hidden, const int32_t* positions, co
   const bool streamed = flags & SIDP_STREAMED;
   h->timing = (flags & SIDP_TIMING) != 0;
   h->step_batch = batch;
+  h->step_streamed = streamed;
   hipStream_t cs = (hipStream_t)compute, cp = (hipStream_t)copy;
   if (streamed && (!h->slots || cp == cs)) return SIDP_EINVAL;
   HIPCHK(h, begin_call(h, cs));
@@ -859,6 +862,7 @@ int sidp_decode_step(sidp_handle* h, float* hidden, const int32_t* positions, co
     }
   }
   HIPCHK(h, finish_call(h, cs));
+  h->step_streamed = false;
   return SIDP_OK;
 }
 

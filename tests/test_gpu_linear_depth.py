@@ -1,0 +1,92 @@
+"""The projection kernel's k loop at the sizes where its pipeline can go wrong:
+fewer k-tiles than the loop keeps in flight, every remainder of its four-tile
+body, ragged last k-tiles, each row-block height and workgroup width, idle
+column groups. Compared with float64 on every element: a sum of k products of
+bf16 numbers accumulated in fp32 is within 2^-20 of sum |x w| of the exact one,
+plus half a bf16 spacing (2^-9 of the value) where the output is bf16."""
+
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+def _run(lib, m, n, k, epi, x):
+    g = torch.Generator(device="cuda").manual_seed(m * 31 + n + k * 7 + epi)
+    w = [(0.02 * torch.randn(n, k, device="cuda", generator=g)).bfloat16() for _ in range(2 if epi == 2 else 1)]
+    cols = 2 * (-(-n // 32) * 32) if epi == 2 else n
+    packed = torch.empty(lib.sidp_packed_bytes(cols, k), dtype=torch.uint8, device="cuda")
+    if epi == 2:
+        lib.sidp_pack_gate_up(w[0], w[1], n, k, packed)
+    else:
+        lib.sidp_pack_linear(w[0], n, k, packed)
+    out = torch.full((m, n), float("nan"), device="cuda", dtype=torch.float32 if epi == 1 else torch.bfloat16)
+    resid = torch.randn(m, n, device="cuda", generator=g) if epi == 1 else None
+    lib.sidp_linear_noalloc(x, m, k, packed, n, epi, None, resid, out)
+    torch.cuda.synchronize()
+    return out.double(), [v.double() for v in w], resid
+
+
+def _check(lib, m, n, k, epi, x):
+    got, w, resid = _run(lib, m, n, k, epi, x)
+    xd = x.double()
+    if epi == 2:
+        gate, up = xd @ w[0].t(), xd @ w[1].t()
+        want = torch.nn.functional.silu(gate) * up
+        # |silu'| <= 1.1: the gate's error passes through scaled by |up|
+        tol = 2.0 ** -20 * (1.1 * (xd.abs() @ w[0].abs().t()) * up.abs()
+                            + torch.nn.functional.silu(gate).abs() * (xd.abs() @ w[1].abs().t()))
+    else:
+        want, tol = xd @ w[0].t(), 2.0 ** -20 * (xd.abs() @ w[0].abs().t())
+        if resid is not None:
+            want, tol = want + resid.double(), tol + 2.0 ** -23 * resid.double().abs()
+    if epi != 1:
+        tol = tol + 2.0 ** -8 * want.abs() + 2.0 ** -133
+    bad = ~((got - want).abs() <= tol)
+    assert not bool(bad.any()), (m, n, k, epi, int(bad.sum()))
+
+
+def _x(m, k, seed=0):
+    g = torch.Generator(device="cuda").manual_seed(m + k + seed)
+    return (0.5 * torch.randn(m, k, device="cuda", generator=g)).bfloat16()
+
+
+@pytest.mark.parametrize("m", [1, 32, 33, 64, 65, 128, 129, 300])
+def test_every_depth_and_row_block(lib, m):
+    for k in (8, 64, 72, 128, 192, 200, 256, 320, 328, 384, 448, 456, 520, 1000, 4104, 7264):
+        _check(lib, m, 1000, k, 0, _x(m, k))
+    _check(lib, m, 1000, 2056, 1, _x(m, 2056))
+    _check(lib, m, 3032, 7264, 2, _x(m, 7264))
+
+
+@pytest.mark.parametrize("m,n,k,epi", [(200, 28672, 520, 2), (129, 29568, 1032, 2), (260, 28672, 64, 2),
+                                       (200, 45056, 264, 0), (512, 28672, 584, 1), (200, 8192, 25608, 1)])
+def test_wide_workgroups_and_large_weights(lib, m, n, k, epi):
+    _check(lib, m, n, k, epi, _x(m, k))
+
+
+@pytest.mark.parametrize("m", [20, 50, 200])
+def test_rows_stay_apart_with_infinities_and_a_ragged_k(lib, m):
+    """A row of infinities or NaN reaches its own outputs only, also where the
+    pieces of a ragged k-tile run on into the next row."""
+    x = _x(m, 456)
+    ref, _, _ = _run(lib, m, 1000, 456, 0, x)
+    y = x.clone()
+    y[7] = float("nan")
+    y[m - 1] = float("inf")
+    got, _, _ = _run(lib, m, 1000, 456, 0, y)
+    keep = [r for r in range(m) if r not in (7, m - 1)]
+    assert torch.equal(got[keep], ref[keep])
+    assert not bool(torch.isfinite(got[7]).any())
+
+
+def test_activations_at_an_odd_eight_bytes(lib):
+    """Activations that are not 16-byte aligned take the register-staged kernel: the same bits."""
+    x = _x(100, 1032)
+    ref, _, _ = _run(lib, 100, 1000, 1032, 0, x)
+    buf = torch.empty(x.numel() + 4, dtype=torch.bfloat16, device="cuda")
+    y = buf[4:].view(100, 1032)
+    y.copy_(x)
+    assert y.data_ptr() % 16 == 8
+    got, _, _ = _run(lib, 100, 1000, 1032, 0, y)
+    assert torch.equal(got, ref)
