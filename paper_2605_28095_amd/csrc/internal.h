@@ -96,20 +96,16 @@ struct AttnCall {
   KvView kv;
   int region;
   uint16_t* out;      // [B][Hq][D]
-  float* part;        // partials [B][Hkv][max_parts] records of Hq/Hkv*D + 32 floats: o[Hq/Hkv][D], (m, l) per head, pad
-  int max_parts;
+  float* part;        // partials: one record per item of Hq/Hkv*D + 32 floats: o[Hq/Hkv][D], (m, l) per head, pad
   uint32_t* err;
   int num_cus;
-  int32_t* plan;      // work list written by launch_attn_plan: [0] count, [1 + i] b | part << 16
-  int part_tokens;    // partition length, set by launch_attention (attn_part_tokens_for)
+  int32_t* plan;      // work list written by launch_attn_plan
 };
-int attn_part_tokens();  // the partition quantum (and shortest partition)
-int attn_part_tokens_for(int batch, int hkv, int max_tokens, int num_cus);
-size_t attn_ws_bytes(int max_batch, int hq, int hkv, int d, int max_seq);
-size_t attn_plan_bytes(int max_batch, int max_parts);
+size_t attn_ws_bytes(int max_batch, int hq, int hkv, int d, int max_seq, int num_cus);
+size_t attn_plan_bytes(int max_batch, int num_cus);
 // Builds the work list from positions; needed once per set of positions (a
-// decode step shares it across its layers). Reads positions, batch,
-// max_blocks, kv.bs, plan, err.
+// decode step shares it across its layers). Reads positions, batch, hkv,
+// num_cus, max_blocks, kv.bs, plan, err.
 hipError_t launch_attn_plan(const AttnCall& c, hipStream_t s);
 // With `start`/`stop`, the events take the start time of the attention's
 // first kernel and the end time of its last from those kernels' own

@@ -1,11 +1,11 @@
 // Paged grouped-query decode attention on gfx950 (K4).
 //
-// Work is a list of items (sequence b, partition p, KV head g). The partition
-// length is chosen per launch (attn_part_tokens_for): whole sequences when
-// the batch alone gives every workgroup several items, else as many
-// 2048-token multiples as that takes. A planning kernel, run once per set of
-// positions, lists the full partitions first and then each sequence's shorter
-// last partition by decreasing length; a persistent grid of 4-wave workgroups
+// Work is a list of items (sequence b, partition p, KV head g). A planning
+// kernel, run once per set of positions, chooses the partition length: whole
+// sequences when the batch alone gives every workgroup several items, else a
+// length that follows the tokens these positions leave to each workgroup.
+// It lists the full partitions first and then each sequence's shorter last
+// partition by decreasing length; a persistent grid of 4-wave workgroups
 // walks that list in snake order (workgroup w takes items w, 2G - 1 - w,
 // 2G + w, ...), which keeps the workgroups' totals within about one short item
 // of each other. Within an item each wave owns a quarter of the tokens,
@@ -28,124 +28,169 @@
 
 namespace sidp {
 
-constexpr int kPartQuantum = 2048;  // partition lengths are multiples of this
 constexpr float kLog2e = 1.4426950408889634f;
 
-int attn_part_tokens() { return kPartQuantum; }
-
-// Partition length of a launch. Whole sequences (no partial records and no
-// combine) when batch x Hkv items already give each of the 2 x CUs persistent
-// workgroups four of them; otherwise the longest sequence the block tables
-// allow is cut into as many pieces as that takes, rounded up to the quantum.
-// Partials written for a later merge cost HBM writes beside the KV stream
-// that slow it by more than their bytes, so fewer partitions are better as
-// long as the workgroups stay balanced.
-int attn_part_tokens_for(int batch, int hkv, int max_tokens, int num_cus) {
-  const int64_t items = (int64_t)std::max(batch, 1) * std::max(hkv, 1);
-  const int64_t want = 4 * 2 * (int64_t)std::max(num_cus, 1);
-  const int64_t pieces = items >= want ? 1 : (want + items - 1) / items;
-  const int64_t p = (max_tokens + pieces - 1) / pieces;
-  return (int)std::max<int64_t>(kPartQuantum, (p + kPartQuantum - 1) / kPartQuantum * kPartQuantum);
+// A launch is left whole (no partial records and no combine) when batch x Hkv
+// items already give each of the 2 x CUs persistent workgroups four of them:
+// partials written for a later merge cost HBM writes beside the KV stream that
+// slow it by more than their bytes, so whole sequences win as long as the
+// workgroups stay balanced. And when no sequence can be longer than kWholeTokens,
+// which one workgroup reads in about the time the combine's launch takes (16
+// sequences of 256-512 tokens: 20.0 us whole, 21.6 split).
+constexpr int kWholeTokens = 768;
+static bool attn_whole(const AttnCall& c) {
+  return c.max_blocks * c.kv.bs <= kWholeTokens ||
+         (int64_t)c.batch * c.hkv >= 4 * 2 * (int64_t)std::max(c.num_cus, 1);
 }
 
-// One partial record per (sequence, KV head, partition): the group's outputs
+// Partition length of a split launch whose positions leave `mean` tokens of one
+// KV head to each of the persistent workgroups: the longest 2^k or 3 * 2^k of at
+// least kMinLen tokens within kShare (kShareLong from kLongMean on) times the
+// mean. A workgroup alone reads five times as fast as its share of HBM when all
+// read, so uneven items level out by themselves and few long items cost less
+// than the starts, merges and records of many short ones, until one item takes
+// as long as the whole launch should. Measured on the 70B heads (us a call, at
+// the length taken / at 2048 tokens, the multiple taken before): 1 sequence of
+// 2000 (mean 31, 256 taken) 18.9 / 29.3, 1 of 8000 (125, 256) 24.8 / 35.5, 2 of
+// 4-8K (190, 512) 25.2 / 36.2, 8 of 0.5-2K (160, 384) 26.4 / 33.9, 5 of 4-8K
+// (480, 1024) 37.1 / 43.0, 16 of 1-8K (1150, 3072) 65.8 / 73.0; at 32 of 1-8K
+// (2300) 2048 is the best (119; 3072 122, 6144 130), at 64 (4600) 4096 204
+// against 216 for 2048 and 210 whole, at 128 (9200) 8192 393 against 421.
+constexpr int kMinLen = 256;
+constexpr float kShare = 2.7f, kShareLong = 1.3f, kLongMean = 1500.f;
+constexpr int kMaxLen = 1 << 20;  // no sequence is longer
+
+__device__ __forceinline__ int split_len(float mean) {
+  const int x = (int)fminf(mean * (mean < kLongMean ? kShare : kShareLong), (float)kMaxLen);
+  if (x <= kMinLen) return kMinLen;
+  const int p = 1 << (31 - __builtin_clz(x));
+  return p + p / 2 <= x ? p + p / 2 : p;
+}
+
+// Most items a split launch lists, and so the partial records it can need. A
+// length is above 2/3 of its bound, so the full partitions number below 1.5 /
+// kShareLong = 1.2 per workgroup; the sequences' last ones add fewer than 4.
+static int attn_item_cap(int num_cus) { return 6 * 2 * std::max(num_cus, 1); }
+
+// One partial record per item of a split launch: the group's outputs
 // o[group][D], then a 128-byte line with (m, l) of each query head, zero
 // padded. Records are whole cache lines (group * D is a multiple of 64), so
 // every write of a record covers whole lines: HBM has no write mask, and a
 // partly written line costs the memory controller a read-modify-write.
 static __host__ __device__ inline int attn_rec_floats(int group, int d) { return group * d + 32; }
 
-size_t attn_ws_bytes(int max_batch, int hq, int hkv, int d, int max_seq) {
-  const int parts = (max_seq + kPartQuantum - 1) / kPartQuantum;
-  return (size_t)max_batch * hkv * parts * attn_rec_floats(hq / hkv, d) * sizeof(float);
+size_t attn_ws_bytes(int max_batch, int hq, int hkv, int d, int max_seq, int num_cus) {
+  const int64_t finest = (int64_t)max_batch * hkv * ((max_seq + kMinLen - 1) / kMinLen);
+  return (size_t)std::min<int64_t>(finest, attn_item_cap(num_cus)) * attn_rec_floats(hq / hkv, d) * sizeof(float);
 }
 
-size_t attn_plan_bytes(int max_batch, int max_parts) { return (1 + (size_t)max_batch * max_parts) * sizeof(int32_t); }
+// The plan: [0] entries listed, [1] partition length, then for each sequence
+// the index of its first full partition and of its last, shorter one, then the
+// entries, b | part << 16.
+static int plan_entries(int batch) { return 2 + 2 * batch; }
 
-// The work list. plan[0] = number of (sequence, partition) entries; entry i is
-// plan[1 + i] = b | part << 16. Full partitions (ptok tokens) come first, in
-// (b, part) order; then the last, shorter partition of every sequence that
-// has one, by decreasing length and then increasing b (a bitonic sort in
-// LDS). Positions outside a sequence's block table give no entries and set
-// the position error bit.
-__global__ void __launch_bounds__(256) k_attn_plan(const int32_t* __restrict__ positions, int batch, int np2,
-                                                   int max_tokens, int ptok, int32_t* __restrict__ plan,
+size_t attn_plan_bytes(int max_batch, int num_cus) {
+  return (size_t)(plan_entries(max_batch) + std::max(max_batch, attn_item_cap(num_cus))) * sizeof(int32_t);
+}
+
+__device__ __forceinline__ int wave_sum_i(int v) {
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
+  return v;
+}
+
+// Writes the plan. Full partitions come first, in (b, part) order; then the
+// last, shorter partition of every sequence that has one, by decreasing length
+// and then increasing b. Positions outside a sequence's block table give no
+// entries and set the position error bit.
+//
+// A latency chain on an otherwise idle chip, so short: every workgroup derives
+// the totals from all positions for itself, and places only its own 64
+// sequences, each one's rank among the short partitions counted by four threads
+// (a bitonic sort by one workgroup took 10 us at 256 sequences; this 4).
+constexpr int kPlanSeqs = 64;  // sequences placed per workgroup
+__global__ void __launch_bounds__(256) k_attn_plan(const int32_t* __restrict__ positions, int batch, int max_tokens,
+                                                   int hkv, int G, int whole, int32_t* __restrict__ plan,
                                                    uint32_t* __restrict__ err) {
-  extern __shared__ int lds_plan[];
-  int* s_key = lds_plan;     // [np2] tokens in the last partition (0: none)
-  int* s_b = s_key + np2;    // [np2] its sequence
-  int* s_full = s_b + np2;   // [batch] full partitions of each sequence
-  __shared__ int s_scan[256];
-  __shared__ int s_npart;
-  const int t = threadIdx.x;
-  if (t == 0) s_npart = 0;
-  __syncthreads();
-  for (int b = t; b < np2; b += 256) {
-    int full = 0, rem = 0;
-    if (b < batch) {
-      const int seq = positions[b] + 1;
-      if (seq >= 1 && seq <= max_tokens) {
-        full = seq / ptok;
-        rem = seq % ptok;
-      } else {
-        atomicOr(err, SIDP_DEVERR_POSITION);
-      }
-      s_full[b] = full;
-      if (rem > 0) atomicAdd(&s_npart, 1);
-    }
-    s_key[b] = rem;
-    s_b[b] = b;
+  // [batch rounded up to 16] each: keys (length << 12 | 4095 - b) of the short partitions, tokens of the sequences
+  extern __shared__ __attribute__((aligned(16))) uint32_t s_key[];
+  __shared__ int s_sum[4];
+  __shared__ int s_scan[4];
+  __shared__ int s_short[4];
+  const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
+  const int padded = (batch + 15) & ~15;
+  int* s_seq = (int*)(s_key + padded);
+  const int per = (batch + 255) / 256;  // thread t owns sequences [b0, b1)
+  const int b0 = min(t * per, batch), b1 = min(b0 + per, batch);
+  for (int b = b0; b < b1; b++) {
+    const int n = positions[b] + 1;
+    s_seq[b] = n >= 1 && n <= max_tokens ? n : 0;
   }
-  __syncthreads();
-  // exclusive prefix of the full counts; thread t owns sequences [t * per, t * per + per)
-  const int per = (batch + 255) / 256;
-  int local = 0;
-  for (int i = 0; i < per; i++) {
-    const int b = t * per + i;
-    if (b < batch) local += s_full[b];
-  }
-  s_scan[t] = local;
-  __syncthreads();
-  for (int off = 1; off < 256; off <<= 1) {
-    const int v = t >= off ? s_scan[t - off] : 0;
+  int ptok = kMaxLen;
+  if (!whole) {
+    int sum = 0;
+    for (int b = b0; b < b1; b++) sum += s_seq[b];
+    // in units of 16 tokens: a split launch has fewer than 2048 sequences of at most 2^20 tokens
+    sum = wave_sum_i((sum + 15) / 16);
+    if (lane == 0) s_sum[wave] = sum;
     __syncthreads();
-    s_scan[t] += v;
-    __syncthreads();
+    ptok = split_len(16.f * (float)hkv * (float)(s_sum[0] + s_sum[1] + s_sum[2] + s_sum[3]) / (float)G);
   }
-  int run = s_scan[t] - local;
-  for (int i = 0; i < per; i++) {
-    const int b = t * per + i;
-    if (b < batch) {
-      for (int p = 0; p < s_full[b]; p++) plan[1 + run + p] = b | (p << 16);
-      run += s_full[b];
-    }
+  // full partitions of each sequence, their exclusive prefix, and the keys of the short ones
+  int local = 0, shorts = 0;
+  for (int b = b0; b < b1; b++) {
+    const int rem = s_seq[b] % ptok;
+    local += s_seq[b] / ptok;
+    shorts += rem > 0;
+    s_key[b] = rem > 0 ? ((uint32_t)rem << 12 | (uint32_t)(4095 - b)) : 0u;
   }
-  const int nfull = s_scan[255];
-  // bitonic sort of (length descending, b ascending)
-  for (int k = 2; k <= np2; k <<= 1) {
-    for (int j = k >> 1; j > 0; j >>= 1) {
-      __syncthreads();
-      for (int i = t; i < np2; i += 256) {
-        const int l = i ^ j;
-        if (l > i) {
-          const int ki = s_key[i], kl = s_key[l], bi = s_b[i], bl = s_b[l];
-          const bool i_first = ki > kl || (ki == kl && bi < bl);
-          if (((i & k) == 0) != i_first) {
-            s_key[i] = kl;
-            s_key[l] = ki;
-            s_b[i] = bl;
-            s_b[l] = bi;
-          }
-        }
-      }
-    }
+  for (int b = batch + t; b < padded; b += 256) s_key[b] = 0u;
+  int incl = local;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int v = __shfl_up(incl, o, 64);
+    if (lane >= o) incl += v;
   }
+  shorts = wave_sum_i(shorts);
+  if (lane == 63) s_scan[wave] = incl;
+  if (lane == 0) s_short[wave] = shorts;
   __syncthreads();
-  for (int i = t; i < s_npart; i += 256) {
-    const int b = s_b[i];
-    plan[1 + nfull + i] = b | (s_full[b] << 16);
+  const int nfull = s_scan[0] + s_scan[1] + s_scan[2] + s_scan[3];
+  int run = incl - local;
+  for (int w = 0; w < wave; w++) run += s_scan[w];
+  if (blockIdx.x == 0 && t == 0) {
+    plan[0] = nfull + s_short[0] + s_short[1] + s_short[2] + s_short[3];
+    plan[1] = ptok;
   }
-  if (t == 0) plan[0] = nfull + s_npart;
+  int32_t* first = plan + 2;
+  int32_t* last = first + batch;
+  int32_t* entries = last + batch;
+  const int lo = blockIdx.x * kPlanSeqs, hi = min(batch, lo + kPlanSeqs);
+  for (int b = b0; b < b1; b++) {
+    const int full = s_seq[b] / ptok;
+    if (b >= lo && b < hi) {
+      if (s_seq[b] == 0) atomicOr(err, SIDP_DEVERR_POSITION);
+      first[b] = run;
+      for (int p = 0; p < full; p++) entries[run + p] = b | (p << 16);
+    }
+    run += full;
+  }
+  // rank of this workgroup's short partitions: four threads a sequence, each over a quarter of the keys
+  const int b = lo + (t >> 2);
+  const uint32_t mine = b < hi ? s_key[b] : 0u;
+  int rank = 0;
+  const int q = padded / 4;
+  const u32x4_t* keys = (const u32x4_t*)(s_key + (t & 3) * q);
+  for (int i = 0; i < q / 4; i++) {
+    const u32x4_t k = keys[i];
+    rank += (k[0] > mine) + (k[1] > mine) + (k[2] > mine) + (k[3] > mine);
+  }
+  rank += __shfl_xor(rank, 1, 64);
+  rank += __shfl_xor(rank, 2, 64);
+  if ((t & 3) == 0 && mine) {
+    last[b] = nfull + rank;
+    entries[nfull + rank] = b | ((s_seq[b] / ptok) << 16);
+  }
 }
 
 template <int D>
@@ -277,12 +322,6 @@ __device__ __forceinline__ void compute_chunk(const Chunk<D>& c, const bf16x8_t 
   }
 }
 
-__device__ __forceinline__ int seq_parts(const AttnCall& a, int b) {
-  const int seq = a.positions[b] + 1;
-  if (seq < 1 || seq > a.max_blocks * a.kv.bs) return 0;  // position outside its block table
-  return (seq + a.part_tokens - 1) / a.part_tokens;
-}
-
 // Item i of the work list is (entry i / Hkv of the plan, KV head i % Hkv).
 // Two 4-wave workgroups per CU; a wave holds 218 VGPRs (224 allocated), so
 // two of them and a slot-fill wave (at most 48) fit in a SIMD's 512.
@@ -300,6 +339,8 @@ __global__ void __launch_bounds__(256, 2) k_attn(AttnCall a) {
 
   cint32_t* plan = (cint32_t*)a.plan;
   const int total_items = plan[0] * a.hkv;
+  const int part_tokens = plan[1];
+  cint32_t* entries = plan + 2 + 2 * a.batch;
   const float scale = kLog2e / sqrtf((float)D);
   const int64_t region_blk = (int64_t)a.region * a.kv.nblk;
   cint32_t* positions = (cint32_t*)a.positions;
@@ -310,21 +351,21 @@ __global__ void __launch_bounds__(256, 2) k_attn(AttnCall a) {
     cint32_t* bt;
   };
   auto get_item = [&](int item, Item& it) {
-    const int e = plan[1 + item / a.hkv];
+    const int e = entries[item / a.hkv];
     it.g = item % a.hkv;
     it.b = e & 0xffff;
     it.part = e >> 16;
     it.seq = positions[it.b] + 1;
-    it.nparts = (it.seq + a.part_tokens - 1) / a.part_tokens;
+    it.nparts = (it.seq + part_tokens - 1) / part_tokens;
     it.bt = (cint32_t*)(a.block_tables + (int64_t)it.b * a.max_blocks);
     // the partition's tokens split evenly over the four waves in whole pairs of
     // 32-token chunks (only the last wave's remainder can be an odd count, whose
     // masked extra chunk re-reads HBM: non-temporal loads leave nothing in L2),
     // so a sequence's shorter last partition keeps all four waves loading
-    const int len = min(it.seq - it.part * a.part_tokens, a.part_tokens);
+    const int len = min(it.seq - it.part * part_tokens, part_tokens);
     const int share = ((len + 3) / 4 + 63) / 64 * 64;
-    it.tb = it.part * a.part_tokens + wave * share;
-    it.te = min(it.tb + share, it.seq);
+    it.tb = it.part * part_tokens + wave * share;
+    it.te = min(it.tb + share, it.part * part_tokens + len);
   };
   // the r-th item of this workgroup in snake order over the sorted list
   auto item_of = [&](int r) {
@@ -370,7 +411,7 @@ __global__ void __launch_bounds__(256, 2) k_attn(AttnCall a) {
     for (int kk = 0; kk < KK; kk++) asm volatile("" ::"v"(qb[kk]));
     Chunk<D> ca, cb;
     // (a wave without tokens in its first item reads the item's first chunk: masked)
-    load_chunk<D>(a, ChunkSrc{cur.bt, cur.seq, cur.g, cur.tb < cur.te ? cur.tb : cur.part * a.part_tokens}, region_blk,
+    load_chunk<D>(a, ChunkSrc{cur.bt, cur.seq, cur.g, cur.tb < cur.te ? cur.tb : cur.part * part_tokens}, region_blk,
                   k_lane, v_lane, bad, ca);
     for (;;) {
       const int nitem = item_of(round + 1);
@@ -391,7 +432,7 @@ __global__ void __launch_bounds__(256, 2) k_attn(AttnCall a) {
       auto src_of = [&](int i) -> ChunkSrc {
         if (i < n) return ChunkSrc{cur.bt, cur.seq, cur.g, cur.tb + 32 * i};
         if (i == n2 && pf) return ChunkSrc{nx.bt, nx.seq, nx.g, nx.tb};
-        return ChunkSrc{cur.bt, cur.seq, cur.g, n > 0 ? cur.tb + 32 * (n - 1) : cur.part * a.part_tokens};
+        return ChunkSrc{cur.bt, cur.seq, cur.g, n > 0 ? cur.tb + 32 * (n - 1) : cur.part * part_tokens};
       };
 
       float m_run = -INFINITY, l_run = 0.f;
@@ -428,7 +469,7 @@ __global__ void __launch_bounds__(256, 2) k_attn(AttnCall a) {
       {
         const int64_t row0 = (int64_t)cur.b * a.hq + cur.g * group;  // the group's first query head
         const int rf = attn_rec_floats(group, D);
-        float* rec = a.part + ((int64_t)(cur.b * a.hkv + cur.g) * a.max_parts + cur.part) * rf;
+        float* rec = a.part + (int64_t)item * rf;
         for (int i = threadIdx.x; i < group * D; i += 256) {
           const int hh = i / D, d = i % D;
           float M = -INFINITY;
@@ -475,27 +516,59 @@ __global__ void __launch_bounds__(256, 2) k_attn(AttnCall a) {
 
 // Log-sum-exp merge of a sequence's partitions: one workgroup per (KV head,
 // sequence) covering the group's query heads, four dims per thread (16-byte
-// loads from the partial records). Partitions are summed in index order.
+// loads from the partial records). Partitions are summed in index order. Bound
+// by the latency of its loads, so none waits for another: the maxima come
+// first, 16 partitions at a time, then every record's terms independently.
 template <int D>
 __global__ void __launch_bounds__(256) k_attn_combine(AttnCall a) {
+  __shared__ float s_max[16][17];
   const int g = blockIdx.x, b = blockIdx.y;
   const int group = a.hq / a.hkv;
-  const int nparts = seq_parts(a, b);
+  cint32_t* plan = (cint32_t*)a.plan;
+  const int part_tokens = plan[1];
+  const int seq = a.positions[b] + 1;
+  if (seq < 1 || seq > a.max_blocks * a.kv.bs) return;  // position outside its block table
+  const int full = seq / part_tokens, nparts = full + (seq % part_tokens > 0);
   if (nparts <= 1) return;
   const int rf = attn_rec_floats(group, D);
-  const float* recs = a.part + ((int64_t)b * a.hkv + g) * a.max_parts * rf;  // partition j at j * rf
+  // records of partitions 0 .. full - 1 are hkv * rf floats apart; the short last one has its own place
+  const float* recs = a.part + ((int64_t)plan[2 + b] * a.hkv + g) * rf;
+  const float* tail = a.part + (nparts > full ? ((int64_t)plan[2 + a.batch + b] * a.hkv + g) * rf : 0);
+  auto rec_of = [&](int j) { return j < full ? recs + (int64_t)j * a.hkv * rf : tail; };
+  {
+    const int hh = threadIdx.x & 15;  // (m, l) pairs past the group are zero padding
+    float M = -INFINITY;
+#pragma unroll 4
+    for (int j = threadIdx.x >> 4; j < nparts; j += 16) M = fmaxf(M, rec_of(j)[group * D + 2 * hh]);
+    s_max[threadIdx.x >> 4][hh] = M;
+    __syncthreads();
+  }
   for (int i = threadIdx.x; i < group * (D / 4); i += 256) {
     const int hh = i / (D / 4), d = (i % (D / 4)) * 4;
-    const float* ml = recs + group * D + 2 * hh;  // (m, l) of head hh, partition 0
+    const int ml = group * D + 2 * hh;  // (m, l) of head hh in a record
     float M = -INFINITY;
-    for (int j = 0; j < nparts; j++) M = fmaxf(M, ml[j * rf]);
+#pragma unroll
+    for (int j = 0; j < 16; j++) M = fmaxf(M, s_max[j][hh]);
     float L = 0.f;
     f32x4_t O = {0.f, 0.f, 0.f, 0.f};
-    for (int j = 0; j < nparts; j++) {
-      const float f = exp2f(ml[j * rf] - M);
-      L += ml[j * rf + 1] * f;
-      const f32x4_t v = *(const f32x4_t*)(recs + j * rf + hh * D + d);
-      O += v * f;
+    for (int j0 = 0; j0 < nparts; j0 += 8) {
+      float m[8], l[8];
+      f32x4_t v[8];
+#pragma unroll
+      for (int j = 0; j < 8; j++) {
+        const float* r = rec_of(min(j0 + j, nparts - 1));
+        m[j] = r[ml];
+        l[j] = r[ml + 1];
+        v[j] = *(const f32x4_t*)(r + hh * D + d);
+      }
+#pragma unroll
+      for (int j = 0; j < 8; j++) {
+        if (j0 + j < nparts) {
+          const float f = exp2f(m[j] - M);
+          L += l[j] * f;
+          O += v[j] * f;
+        }
+      }
     }
     uint16_t* o = a.out + ((int64_t)b * a.hq + g * group + hh) * D + d;
     *(uint32_t*)o = pack_bf2(O[0] / L, O[1] / L);
@@ -505,18 +578,16 @@ __global__ void __launch_bounds__(256) k_attn_combine(AttnCall a) {
 
 hipError_t launch_attn_plan(const AttnCall& c, hipStream_t s) {
   if (c.batch <= 0) return hipSuccess;
-  int np2 = 1;
-  while (np2 < c.batch) np2 <<= 1;
-  const size_t lds = (size_t)(2 * np2 + c.batch) * sizeof(int);
-  if (lds > 64 * 1024) return hipErrorInvalidValue;
-  const int max_tokens = c.max_blocks * c.kv.bs;
-  const int ptok = attn_part_tokens_for(c.batch, c.hkv, max_tokens, c.num_cus);
-  k_attn_plan<<<1, 256, lds, s>>>(c.positions, c.batch, np2, max_tokens, ptok, c.plan, c.err);
+  if (c.batch > 4096) return hipErrorInvalidValue;
+  const size_t lds = (size_t)((c.batch + 15) & ~15) * 2 * sizeof(uint32_t);
+  k_attn_plan<<<(c.batch + kPlanSeqs - 1) / kPlanSeqs, 256, lds, s>>>(
+      c.positions, c.batch, c.max_blocks * c.kv.bs, c.hkv, 2 * c.num_cus, attn_whole(c), c.plan,
+      c.err);
   return hipGetLastError();
 }
 
 template <int D>
-static hipError_t launch_d(const AttnCall& c, int grid, int parts, hipStream_t s, hipEvent_t start, hipEvent_t stop) {
+static hipError_t launch_d(const AttnCall& c, int grid, bool split, hipStream_t s, hipEvent_t start, hipEvent_t stop) {
   const size_t lds = (size_t)(128 + 4 * 16 * (D + 1)) * 4;
   if (lds > 64 * 1024) {
     hipError_t e = hipFuncSetAttribute((const void*)k_attn<D>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -524,30 +595,26 @@ static hipError_t launch_d(const AttnCall& c, int grid, int parts, hipStream_t s
   }
   if (!start && !stop) {
     k_attn<D><<<grid, 256, lds, s>>>(c);
-    if (parts > 1) k_attn_combine<D><<<dim3(c.hkv, c.batch), 256, 0, s>>>(c);
+    if (split) k_attn_combine<D><<<dim3(c.hkv, c.batch), 256, 0, s>>>(c);
     return hipGetLastError();
   }
   // timed: the events ride on the kernels' own dispatches
   AttnCall arg = c;
   void* args[] = {&arg};
   hipError_t e = hipExtLaunchKernel((const void*)k_attn<D>, dim3(grid), dim3(256), args, lds, s, start,
-                                    parts > 1 ? nullptr : stop, 0);
-  if (e != hipSuccess || parts <= 1) return e;
+                                    split ? nullptr : stop, 0);
+  if (e != hipSuccess || !split) return e;
   return hipExtLaunchKernel((const void*)k_attn_combine<D>, dim3(c.hkv, c.batch), dim3(256), args, 0, s, nullptr, stop,
                             0);
 }
 
-hipError_t launch_attention(const AttnCall& call, hipStream_t s, hipEvent_t start, hipEvent_t stop) {
-  if (call.batch <= 0) return hipSuccess;
-  AttnCall c = call;
-  const int max_tokens = c.max_blocks * c.kv.bs;
-  c.part_tokens = attn_part_tokens_for(c.batch, c.hkv, max_tokens, c.num_cus);  // as the plan was built
-  const int parts = (max_tokens + c.part_tokens - 1) / c.part_tokens;
-  if (parts > c.max_parts) return hipErrorInvalidValue;
+hipError_t launch_attention(const AttnCall& c, hipStream_t s, hipEvent_t start, hipEvent_t stop) {
+  if (c.batch <= 0) return hipSuccess;
   if (c.hq / c.hkv > 16) return hipErrorInvalidValue;
+  const bool split = !attn_whole(c);
   const int grid = 2 * c.num_cus;  // persistent: two 4-wave workgroups per CU
-  if (c.d == 128) return launch_d<128>(c, grid, parts, s, start, stop);
-  if (c.d == 64) return launch_d<64>(c, grid, parts, s, start, stop);
+  if (c.d == 128) return launch_d<128>(c, grid, split, s, start, stop);
+  if (c.d == 64) return launch_d<64>(c, grid, split, s, start, stop);
   return hipErrorInvalidValue;
 }
 

@@ -33,6 +33,7 @@ constexpr int64_t kDelayTicks = 20000;  // 200 us of the 100 MHz constant clock
 constexpr int kFillPartAPercent = 25;  // share of a layer's fill issued before its predecessor's attention
 constexpr int kFillSmallBatch = 160;   // below this many rows both fill tiles keep 8 loads per lane in flight
 constexpr int kFillLongBatch = 384;    // from this many rows the projections outlast a gentle tile B
+constexpr int kTableUnit = 2048;  // block tables may be as wide as max_seq_len rounded up to this many tokens
 constexpr int kBurstGrid = 512;        // workgroups of the whole-chip burst copy (SIDP_COPY_BURST)
 
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
@@ -179,7 +180,7 @@ struct sidp_handle {
   float* ws = nullptr;
   size_t ws_bytes = 0;
   float* attn_part = nullptr;
-  int attn_max_parts = 0;
+  int max_table_units = 0;  // widest block table a call may bring, in kTableUnit tokens
   int32_t* attn_plan = nullptr;  // attention work list, rebuilt once per decode step
   // The attention-norm gains of every layer ([L][H] bf16, 16 KB per layer at
   // H = 8192), kept resident beside the pool so that layer l's down-projection
@@ -328,8 +329,9 @@ int sidp_create(const sidp_config* cfg, sidp_handle** out) {
   }
   h->ws_bytes = ws;
   const int max_seq16 = round_up_i(c.max_seq_len, 16);
-  h->attn_max_parts = (max_seq16 + attn_part_tokens() - 1) / attn_part_tokens();
-  const size_t part_bytes = attn_ws_bytes(c.max_batch, c.num_q_heads, c.num_kv_heads, c.head_dim, max_seq16);
+  h->max_table_units = (max_seq16 + kTableUnit - 1) / kTableUnit;
+  const size_t part_bytes = attn_ws_bytes(c.max_batch, c.num_q_heads, c.num_kv_heads, c.head_dim,
+                                          h->max_table_units * kTableUnit, h->num_cus);
   struct {
     void** p;
     size_t bytes;
@@ -341,7 +343,7 @@ int sidp_create(const sidp_config* cfg, sidp_handle** out) {
       {(void**)&h->act, B * (size_t)c.ffn_dim * 2},
       {(void**)&h->ws, std::max<size_t>(ws, 256)},
       {(void**)&h->attn_part, std::max<size_t>(part_bytes, 256)},
-      {(void**)&h->attn_plan, attn_plan_bytes(c.max_batch, h->attn_max_parts)},
+      {(void**)&h->attn_plan, attn_plan_bytes(c.max_batch, h->num_cus)},
       {(void**)&h->g_attn_all, (size_t)c.num_layers * H * 2},
       {(void**)&h->cas_y, B * H * 4},
       {(void**)&h->rope_cos, (size_t)c.max_seq_len * (D / 2) * 4},
@@ -635,7 +637,6 @@ static hipError_t run_attn_half(sidp_handle* h, const uint8_t* wb, int layer, fl
   a.region = layer % h->regions;
   a.out = h->o;
   a.part = h->attn_part;
-  a.max_parts = h->attn_max_parts;
   a.err = h->err;
   a.num_cus = h->num_cus;
   a.plan = h->attn_plan;
@@ -775,8 +776,7 @@ int sidp_decode_step(sidp_handle* h, float* hidden, const int32_t* positions, co
   if (!h->pool || !h->k_cache) return SIDP_ESTATE;
   for (int l = 0; l < c.num_layers; l++)
     if (!h->loaded[l]) return SIDP_ESTATE;
-  const int parts = (max_blocks_per_seq * c.block_size + attn_part_tokens() - 1) / attn_part_tokens();
-  if (parts > h->attn_max_parts) return SIDP_EINVAL;
+  if ((max_blocks_per_seq * c.block_size + kTableUnit - 1) / kTableUnit > h->max_table_units) return SIDP_EINVAL;
   const bool streamed = flags & SIDP_STREAMED;
   h->timing = (flags & SIDP_TIMING) != 0;
   h->step_batch = batch;
@@ -1159,8 +1159,7 @@ int sidp_attention(sidp_handle* h, const void* q, int32_t region, const int32_t*
   if (!h || !q || !positions || !block_tables || !out || batch < 0 || batch > h->cfg.max_batch) return SIDP_EINVAL;
   if (h->poisoned) return SIDP_ESTATE;
   if (!h->k_cache || region < 0 || region >= h->regions || max_blocks_per_seq < 1) return SIDP_EINVAL;
-  const int parts = (max_blocks_per_seq * h->cfg.block_size + attn_part_tokens() - 1) / attn_part_tokens();
-  if (parts > h->attn_max_parts) return SIDP_EINVAL;
+  if ((max_blocks_per_seq * h->cfg.block_size + kTableUnit - 1) / kTableUnit > h->max_table_units) return SIDP_EINVAL;
   AttnCall a;
   a.q = (const uint16_t*)q;
   a.positions = positions;
@@ -1174,7 +1173,6 @@ int sidp_attention(sidp_handle* h, const void* q, int32_t region, const int32_t*
   a.region = region;
   a.out = (uint16_t*)out;
   a.part = h->attn_part;
-  a.max_parts = h->attn_max_parts;
   a.err = h->err;
   a.num_cus = h->num_cus;
   a.plan = h->attn_plan;

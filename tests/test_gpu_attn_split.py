@@ -1,0 +1,36 @@
+"""The attention's work list and split sequences: partition lengths from the
+shortest on, sequences that end at a partition boundary or one token past it,
+several planning workgroups, and a list whose sequences are mostly whole.
+Compared with the oracle as the other attention cases are."""
+
+import numpy as np
+import pytest
+
+import synth
+from gpu_helpers import assert_bf16_within_ulp
+from test_gpu_kernels import _attn_oracle, _attn_run, _attn_setup
+
+pytestmark = pytest.mark.gpu
+
+
+def _mixed(n, hi, seed):
+    return np.random.default_rng(seed).integers(1, hi + 1, n).tolist()
+
+
+@pytest.mark.parametrize("hq,hkv,d,seqs", [
+    (4, 2, 64, [2000]),                                        # shortest partitions (256 tokens), seven and a rest
+    (8, 1, 128, [768, 769, 1024, 1025, 256, 257, 1, 255]),     # ends at and past partition boundaries
+    (16, 1, 128, [5000, 17, 3000]),                            # the largest group
+    (64, 8, 128, [4096, 8192, 4097, 5000, 6143]),              # 1024-token partitions
+    (4, 2, 64, _mixed(65, 1500, 1)),                           # two planning workgroups, the second with one sequence
+    (4, 2, 64, _mixed(300, 2500, 2)),                          # five, per-thread runs of two sequences
+    (4, 2, 64, [1] * 70 + [9000] + [2] * 70),                  # one long sequence among short ones
+    (2, 1, 64, _mixed(700, 900, 3)),                           # mostly one partition each, past the whole-launch width
+])
+def test_split_attention_parity(lib, hq, hkv, d, seqs):
+    cfg = synth.get_config("tiny_layer", num_q_heads=hq, num_kv_heads=hkv, head_dim=d)
+    ctx, tables, nblk, k, v, q, maxb = _attn_setup(lib, cfg, seqs)
+    got = _attn_run(lib, cfg, ctx, tables, nblk, k, v, q, maxb)
+    want = _attn_oracle(cfg, ctx, tables, k, v, q)
+    pv = _attn_oracle(cfg, ctx, tables, k, v, q, absv=True)
+    assert_bf16_within_ulp(got, want, what=f"split attention {hq}/{hkv} x {d}", abs_tol=2.0 ** -12 * pv)
