@@ -431,53 +431,65 @@ __global__ void __launch_bounds__(512, 1) k_gemm_lw(GemmArgs a) {
   store_tile<4, EPI, PARTIAL>(a, acc, row0, ng, split, lane);
 }
 
-// Sum split-K partials in split order and apply the epilogue.
-template <int EPI>
-__global__ void k_splitk_reduce(GemmArgs a) {
+// Sum split-K partials in split order and apply the epilogue. VEC columns per
+// thread (4 with 16-byte loads, where the sizes and pointers allow; else 1), one
+// row per blockIdx.y, eight splits' loads in flight. Bound by the partials' read:
+// QKV at 256 rows (3 splits, 31 MB) takes 7.4 us; one column a thread, with a
+// 64-bit division for its row, took 10.4.
+template <int EPI, int VEC>
+__global__ void __launch_bounds__(256) k_splitk_reduce(GemmArgs a) {
+  typedef float vec_t __attribute__((ext_vector_type(VEC)));
   const int NP = a.NG * 64;
-  const int cols = EPI == SIDP_EPI_SWIGLU ? a.N : a.N;  // output columns
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (int64_t)a.M * cols) return;
-  const int row = (int)(idx / cols), c = (int)(idx % cols);
-  if (EPI == SIDP_EPI_SWIGLU) {
-    const int pc = (c / 32) * 64 + (c % 32);
-    float g = 0.f, u = 0.f;
-    for (int s0 = 0; s0 < a.splits; s0 += 4) {  // four partials in flight, summed in split order
-      float pg[4], pu[4];
+  const int row = blockIdx.y, c = (blockIdx.x * 256 + threadIdx.x) * VEC;
+  if (c >= a.N) return;
+  const int64_t idx = (int64_t)row * a.N + c;
+  const int64_t step = (int64_t)a.M * NP;  // from one split's partials to the next's
+  auto sum = [&](const float* p) {
+    vec_t v = 0.f;
+    for (int s0 = 0; s0 < a.splits; s0 += 8) {
+      vec_t pv[8];
 #pragma unroll
-      for (int j = 0; j < 4; j++)
-        if (s0 + j < a.splits) {
-          const float* p = a.ws + ((int64_t)(s0 + j) * a.M + row) * NP + pc;
-          pg[j] = p[0];
-          pu[j] = p[32];
-        }
+      for (int j = 0; j < 8; j++)
+        if (s0 + j < a.splits) pv[j] = *(const vec_t*)(p + (s0 + j) * step);
 #pragma unroll
-      for (int j = 0; j < 4; j++)
-        if (s0 + j < a.splits) {
-          g += pg[j];
-          u += pu[j];
-        }
-    }
-    ((uint16_t*)a.out)[idx] = f2bf(silu_f(g) * u);
-  } else {
-    const int pc = (c / 64) * 64 + (c % 64);  // packed column of output n (identity)
-    float v = 0.f;
-    for (int s0 = 0; s0 < a.splits; s0 += 4) {  // four partials in flight, summed in split order
-      float pv[4];
-#pragma unroll
-      for (int j = 0; j < 4; j++)
-        if (s0 + j < a.splits) pv[j] = a.ws[((int64_t)(s0 + j) * a.M + row) * NP + pc];
-#pragma unroll
-      for (int j = 0; j < 4; j++)
+      for (int j = 0; j < 8; j++)
         if (s0 + j < a.splits) v += pv[j];
     }
-    if (EPI == SIDP_EPI_BF16) {
-      if (a.bias) v += bf2f(a.bias[c]);
-      ((uint16_t*)a.out)[idx] = f2bf(v);
-    } else {
-      ((float*)a.out)[idx] = a.resid ? a.resid[idx] + v : v;
+    return v;
+  };
+  const float* row_ws = a.ws + (int64_t)row * NP;
+  vec_t v;
+  if (EPI == SIDP_EPI_SWIGLU) {
+    const float* p = row_ws + (c / 32) * 64 + (c % 32);  // gate columns, 32 ahead of their up columns
+    const vec_t g = sum(p), u = sum(p + 32);
+#pragma unroll
+    for (int j = 0; j < VEC; j++) v[j] = silu_f(g[j]) * u[j];
+  } else {
+    v = sum(row_ws + c);
+    if (EPI == SIDP_EPI_BF16 && a.bias) {
+#pragma unroll
+      for (int j = 0; j < VEC; j++) v[j] += bf2f(a.bias[c + j]);
     }
   }
+  if (EPI == SIDP_EPI_RESID) {
+    if (a.resid) v = *(const vec_t*)(a.resid + idx) + v;
+    *(vec_t*)((float*)a.out + idx) = v;
+  } else if constexpr (VEC == 4) {
+    *(u32x2_t*)((uint16_t*)a.out + idx) = u32x2_t{pack_bf2(v[0], v[1]), pack_bf2(v[2], v[3])};
+  } else {
+    ((uint16_t*)a.out)[idx] = f2bf(v[0]);
+  }
+}
+
+template <int EPI>
+static hipError_t launch_splitk_reduce(const GemmArgs& a, hipStream_t s) {
+  const size_t align = EPI == SIDP_EPI_RESID ? 16 : 8;
+  const bool vec = a.N % 4 == 0 && (uintptr_t)a.out % align == 0 && (uintptr_t)a.resid % 16 == 0;
+  const int cols = vec ? 1024 : 256;  // per workgroup
+  const dim3 grid((a.N + cols - 1) / cols, a.M);
+  if (vec) k_splitk_reduce<EPI, 4><<<grid, 256, 0, s>>>(a);
+  else k_splitk_reduce<EPI, 1><<<grid, 256, 0, s>>>(a);
+  return hipGetLastError();
 }
 
 // ---------------------------------------------------------------- host side
@@ -696,12 +708,9 @@ hipError_t launch_linear(const LinearCall& c, hipStream_t s) {
   if (fuse_norm && reduce_resid_norm_fits(a.N))
     return launch_reduce_resid_norm(a.ws, a.splits, a.M, a.NG * 64, a.N, (float*)c.out, c.norm_gain, c.norm_eps,
                                     c.norm_out, s);
-  const int64_t outs = (int64_t)a.M * a.N;
-  const unsigned blocks = (unsigned)((outs + 255) / 256);
-  if (c.epilogue == SIDP_EPI_BF16) k_splitk_reduce<SIDP_EPI_BF16><<<blocks, 256, 0, s>>>(a);
-  else if (c.epilogue == SIDP_EPI_RESID) k_splitk_reduce<SIDP_EPI_RESID><<<blocks, 256, 0, s>>>(a);
-  else k_splitk_reduce<SIDP_EPI_SWIGLU><<<blocks, 256, 0, s>>>(a);
-  e = hipGetLastError();
+  if (c.epilogue == SIDP_EPI_BF16) e = launch_splitk_reduce<SIDP_EPI_BF16>(a, s);
+  else if (c.epilogue == SIDP_EPI_RESID) e = launch_splitk_reduce<SIDP_EPI_RESID>(a, s);
+  else e = launch_splitk_reduce<SIDP_EPI_SWIGLU>(a, s);
   if (e != hipSuccess || !fuse_norm) return e;
   return launch_rmsnorm((const float*)c.out, c.norm_gain, c.norm_eps, c.norm_out, a.M, a.N, s);
 }

@@ -90,3 +90,10 @@ def test_activations_at_an_odd_eight_bytes(lib):
     assert y.data_ptr() % 16 == 8
     got, _, _ = _run(lib, 100, 1000, 1032, 0, y)
     assert torch.equal(got, ref)
+
+
+@pytest.mark.parametrize("n,epi", [(1001, 0), (999, 1), (3030, 2), (1002, 0), (4, 1), (1, 0)])
+def test_split_reduction_of_odd_widths(lib, n, epi):
+    """Split-K outputs whose width is no multiple of four columns are reduced one column a thread."""
+    assert lib.sidp_linear_plan(17, n, 4104, epi)["splits"] > 1
+    _check(lib, 17, n, 4104, epi, _x(17, 4104))
