@@ -1,8 +1,12 @@
 // Per-head QK RMSNorm (Qwen3 family), rotary embedding, and the append of the
 // new token's key and value to the paged KV cache (K3), plus the slot mapping
-// slot = block_table[p / bs] * bs + p % bs (K9). One wave per (sequence,
-// head), four heads per workgroup; lane i owns the rotate-half pair
-// (i, i + D/2). The projection output is read either as bf16 or, when the QKV
+// slot = block_table[p / bs] * bs + p % bs (K9). A lane holds 8 consecutive dims
+// of a head, D / 8 lanes a head, so a wave takes 4 heads (8 at D = 64) of one
+// sequence and a workgroup 16 (32); the other half of a rotate-half pair sits
+// D / 16 lanes away. Bound by latency, not bytes: 16-byte loads and stores and
+// several heads to a wave keep a launch at one round of waves on the chip (256
+// sequences of 80 heads with QK-norm 8.1 us; a wave per head, 2 bytes a lane and
+// load, 10.4). The projection output is read either as bf16 or, when the QKV
 // projection left split-K partials, reduced here: the partials are summed in
 // split order, the bias added and the result rounded to bf16, which is the
 // same value the projection's own reduction would have stored.
@@ -11,13 +15,30 @@
 
 namespace sidp {
 
+// 8 bf16 values; ALIGNED: 16-byte aligned, one load.
+template <bool ALIGNED>
+__device__ __forceinline__ void load8(const uint16_t* p, float (&v)[8]) {
+  if (ALIGNED) {
+    const u32x4_t u = *(const u32x4_t*)p;
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+      v[2 * i] = bf2f((uint16_t)(u[i] & 0xffffu));
+      v[2 * i + 1] = bf2f((uint16_t)(u[i] >> 16));
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < 8; i++) v[i] = bf2f(p[i]);
+  }
+}
+
+template <int D, bool ALIGNED>
 __global__ void __launch_bounds__(256) k_rope_append(RopeCall c) {
+  constexpr int kLanes = D / 8;         // lanes of a head
+  constexpr int kHeads = 256 / kLanes;  // heads of a workgroup
   const int b = blockIdx.x;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int D = c.d, half = D >> 1;
   const int heads = c.hq + 2 * c.hkv;
-  const int h = blockIdx.y * 4 + wave;
-  if (h >= heads) return;
+  const int h = blockIdx.y * kHeads + threadIdx.x / kLanes;
+  const int sub = threadIdx.x % kLanes, d0 = sub * 8;  // this lane's dims d0 .. d0 + 7
   const int pos = c.positions[b];
   const int lb = pos >= 0 ? pos / c.kv.bs : -1;
   const bool ok_pos = pos >= 0 && lb < c.max_blocks && pos < c.max_seq;
@@ -27,89 +48,117 @@ __global__ void __launch_bounds__(256) k_rope_append(RopeCall c) {
     if (!ok_pos) atomicOr(c.err, SIDP_DEVERR_POSITION);
     else if (!ok_blk) atomicOr(c.err, SIDP_DEVERR_BLOCK);
   }
+  if (h >= heads) return;  // whole heads at a time: the lanes of a shuffle stay together
   const int off = ok_pos ? pos % c.kv.bs : 0;
   const int rpos = ok_pos ? pos : 0;
   const int64_t region_base = (int64_t)c.region * c.kv.nblk;
-
   const bool is_q = h < c.hq, is_k = !is_q && h < c.hq + c.hkv;
-  const bool act = lane < half;
-  const int col0 = h * D + lane, col1 = col0 + half;
-  uint16_t v0 = 0, v1 = 0;  // the bf16 projection output of this lane's pair
-  if (act) {
-    if (c.ws) {
-      // four splits' partials in flight at a time, summed in split order
-      float s0 = 0.f, s1 = 0.f;
-      for (int sp0 = 0; sp0 < c.splits; sp0 += 4) {
-        float p0[4], p1[4];
+
+  float x[8];  // the bf16 projection output
+  if (c.ws) {
+    // eight splits' partials in flight at a time, summed in split order
+    f32x4_t s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;
+    const float* row = c.ws + (int64_t)b * c.ws_np + h * D + d0;
+    const int64_t step = (int64_t)c.batch * c.ws_np;
+    for (int sp0 = 0; sp0 < c.splits; sp0 += 8) {
+      f32x4_t p0[8], p1[8];
 #pragma unroll
-        for (int j = 0; j < 4; j++)
-          if (sp0 + j < c.splits) {
-            const float* pr = c.ws + ((int64_t)(sp0 + j) * c.batch + b) * c.ws_np;
-            p0[j] = pr[col0];
-            p1[j] = pr[col1];
-          }
+      for (int j = 0; j < 8; j++)
+        if (sp0 + j < c.splits) {
+          p0[j] = *(const f32x4_t*)(row + (sp0 + j) * step);
+          p1[j] = *(const f32x4_t*)(row + (sp0 + j) * step + 4);
+        }
 #pragma unroll
-        for (int j = 0; j < 4; j++)
-          if (sp0 + j < c.splits) {
-            s0 += p0[j];
-            s1 += p1[j];
-          }
-      }
-      if (c.bias) {
-        s0 += bf2f(c.bias[col0]);
-        s1 += bf2f(c.bias[col1]);
-      }
-      v0 = f2bf(s0);
-      v1 = f2bf(s1);
-    } else {
-      const uint16_t* src = c.qkv + (int64_t)b * heads * D;
-      v0 = src[col0];
-      v1 = src[col1];
+      for (int j = 0; j < 8; j++)
+        if (sp0 + j < c.splits) {
+          s0 += p0[j];
+          s1 += p1[j];
+        }
     }
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+      x[i] = s0[i];
+      x[4 + i] = s1[i];
+    }
+    if (c.bias) {
+      float bias[8];
+      load8<ALIGNED>(c.bias + h * D + d0, bias);
+#pragma unroll
+      for (int i = 0; i < 8; i++) x[i] += bias[i];
+    }
+#pragma unroll
+    for (int i = 0; i < 8; i++) x[i] = bf2f(f2bf(x[i]));
+  } else {
+    load8<ALIGNED>(c.qkv + ((int64_t)b * heads + h) * D + d0, x);
   }
   if (!is_q && !is_k) {  // value head: store as is, transposed block layout [d][token]
-    if (act && ok_blk) {
+    if (ok_blk) {
       const int vh = h - c.hq - c.hkv;
       uint16_t* vb = c.kv.v + ((region_base + blk) * c.kv.hkv + vh) * (int64_t)D * c.kv.bs;
-      vb[(int64_t)lane * c.kv.bs + off] = v0;
-      vb[(int64_t)(lane + half) * c.kv.bs + off] = v1;
+#pragma unroll
+      for (int i = 0; i < 8; i++) vb[(int64_t)(d0 + i) * c.kv.bs + off] = f2bf(x[i]);
     }
     return;
   }
-  float x0 = bf2f(v0), x1 = bf2f(v1);
   const uint16_t* gn = is_q ? c.g_q : c.g_k;
   if (gn) {
-    const float ss = wave_sum(x0 * x0 + x1 * x1);
+    float g[8], ss = 0.f;
+    load8<ALIGNED>(gn + d0, g);
+#pragma unroll
+    for (int i = 0; i < 8; i++) ss += x[i] * x[i];
+#pragma unroll
+    for (int o = kLanes / 2; o >= 1; o >>= 1) ss += __shfl_xor(ss, o, 64);
     const float r = 1.0f / sqrtf(ss / (float)D + c.qk_eps);
-    if (act) {
-      x0 = x0 * r * bf2f(gn[lane]);
-      x1 = x1 * r * bf2f(gn[lane + half]);
-    }
+#pragma unroll
+    for (int i = 0; i < 8; i++) x[i] = x[i] * r * g[i];
   }
-  if (!act) return;
-  const float cs = c.rope_cos[(int64_t)rpos * half + lane];
-  const float sn = c.rope_sin[(int64_t)rpos * half + lane];
-  const float y0 = x0 * cs - x1 * sn;
-  const float y1 = x1 * cs + x0 * sn;
+  const int t0 = d0 % (D / 2);  // the pair's angle index
+  const float* cs = c.rope_cos + (int64_t)rpos * (D / 2) + t0;
+  const float* sn = c.rope_sin + (int64_t)rpos * (D / 2) + t0;
+  const float sign = d0 < D / 2 ? -1.f : 1.f;
+  uint32_t y[4];
+#pragma unroll
+  for (int i = 0; i < 8; i += 4) {
+    const f32x4_t cv = *(const f32x4_t*)(cs + i), sv = *(const f32x4_t*)(sn + i) * sign;
+    float o[4];
+#pragma unroll
+    for (int j = 0; j < 4; j++) {
+      const float other = __shfl_xor(x[i + j], kLanes / 2, 64);
+      o[j] = x[i + j] * cv[j] + other * sv[j];
+    }
+    y[i / 2] = pack_bf2(o[0], o[1]);
+    y[i / 2 + 1] = pack_bf2(o[2], o[3]);
+  }
+  const u32x4_t out = {y[0], y[1], y[2], y[3]};
   if (is_q) {
-    uint16_t* qo = c.q_out + ((int64_t)b * c.hq + h) * D;
-    qo[lane] = f2bf(y0);
-    qo[lane + half] = f2bf(y1);
+    uint16_t* qo = c.q_out + ((int64_t)b * c.hq + h) * D + d0;
+    if (ALIGNED) {
+      *(u32x4_t*)qo = out;
+    } else {
+#pragma unroll
+      for (int i = 0; i < 8; i++) qo[i] = (uint16_t)(out[i / 2] >> (16 * (i % 2)));
+    }
   } else if (ok_blk) {
-    // key blocks are [d / 8][token][d % 8]
+    // key blocks are [d / 8][token][d % 8]: the lane's 8 dims are one 16-byte piece
     const int kh = h - c.hq;
     uint16_t* kb = c.kv.k + ((region_base + blk) * c.kv.hkv + kh) * (int64_t)D * c.kv.bs;
-    const int d0 = lane, d1 = lane + half;
-    kb[((d0 >> 3) * c.kv.bs + off) * 8 + (d0 & 7)] = f2bf(y0);
-    kb[((d1 >> 3) * c.kv.bs + off) * 8 + (d1 & 7)] = f2bf(y1);
+    *(u32x4_t*)(kb + (sub * c.kv.bs + off) * 8) = out;
   }
+}
+
+template <int D>
+static hipError_t launch_rope_d(const RopeCall& c, hipStream_t s) {
+  const int per = 256 / (D / 8), heads = c.hq + 2 * c.hkv;
+  const dim3 grid(c.batch, (heads + per - 1) / per);
+  const uintptr_t ptrs = (uintptr_t)c.qkv | (uintptr_t)c.bias | (uintptr_t)c.g_q | (uintptr_t)c.g_k | (uintptr_t)c.q_out;
+  if (ptrs % 16 == 0) k_rope_append<D, true><<<grid, 256, 0, s>>>(c);
+  else k_rope_append<D, false><<<grid, 256, 0, s>>>(c);
+  return hipGetLastError();
 }
 
 hipError_t launch_rope_append(const RopeCall& c, hipStream_t s) {
   if (c.batch <= 0) return hipSuccess;
-  const int heads = c.hq + 2 * c.hkv;
-  k_rope_append<<<dim3(c.batch, (heads + 3) / 4), 256, 0, s>>>(c);
-  return hipGetLastError();
+  return c.d == 128 ? launch_rope_d<128>(c, s) : launch_rope_d<64>(c, s);
 }
 
 __global__ void k_slot_mapping(const int32_t* __restrict__ positions, const int32_t* __restrict__ bt, int max_blocks,
