@@ -1,0 +1,55 @@
+"""Branches of the small kernels: the RMSNorm whose row stays in registers at
+both ends of its range, and the KV append on inputs that are not 16-byte
+aligned (element loads), which must give the aligned call's bits."""
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import synth
+from gpu_helpers import assert_bf16_within_ulp, bits
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("rows,n", [(2, 4092), (2, 4096), (3, 4100), (5, 16384), (2, 16388)])
+def test_rmsnorm_row_lengths(lib, rows, n):
+    g = torch.Generator().manual_seed(rows + n)
+    x = torch.randn(rows, n, generator=g) * 3.0
+    gain = (1 + 0.1 * torch.randn(n, generator=g)).to(torch.bfloat16)
+    out = torch.empty(rows, n, dtype=torch.bfloat16, device="cuda")
+    lib.sidp_rmsnorm(x.cuda(), gain.cuda(), 1e-5, out, rows, n)
+    torch.cuda.synchronize()
+    want = oracle.rms_norm(x.double().numpy(), oracle.bf16_bits_to_f64(bits(gain)), 1e-5)
+    assert_bf16_within_ulp(bits(out), want, what="rmsnorm")
+
+
+@pytest.mark.parametrize("name", ["tiny_layer", "qwen3_32b_layer"])
+def test_rope_append_unaligned_inputs_bitexact(lib, name):
+    cfg = synth.get_config(name, qk_norm=1, num_layers=1)
+    Hq, Hkv, D = cfg["num_q_heads"], cfg["num_kv_heads"], cfg["head_dim"]
+    ctx = np.array([0, 5, 16, 200], np.int32)
+    B, nblk, width = len(ctx), 40, 16
+    bt = torch.tensor(lib.sidp_kv_alloc(ctx, 1, 16, nblk, 3, width), dtype=torch.int32, device="cuda")
+    pos = torch.tensor(ctx, dtype=torch.int32, device="cuda")
+    g = torch.Generator().manual_seed(5)
+    src = [torch.randn(n, generator=g).to(torch.bfloat16) for n in (B * (Hq + 2 * Hkv) * D, D, D)]
+    outs = []
+    for offset in (0, 1):
+        t = [torch.zeros(s.numel() + 8, dtype=torch.bfloat16, device="cuda") for s in src]
+        qkv, gq, gk = (b[offset:offset + s.numel()].copy_(s) for b, s in zip(t, src))
+        qbuf = torch.zeros(B * Hq * D + 8, dtype=torch.bfloat16, device="cuda")
+        q = qbuf[offset:offset + B * Hq * D]
+        kc = torch.zeros(nblk, Hkv, D // 8, 16, 8, dtype=torch.bfloat16, device="cuda")
+        vc = torch.zeros(nblk, Hkv, D, 16, dtype=torch.bfloat16, device="cuda")
+        h = lib.sidp_create(lib.make_config(cfg, B, 2048))
+        try:
+            lib.sidp_kv_attach(h, kc, vc, nblk, 1)
+            lib.sidp_rope_append(h, qkv, pos, bt, width, B, gq, gk, 0, q)
+            lib.sidp_sync(h)
+        finally:
+            lib.sidp_destroy(h)
+        outs.append((q.clone(), kc, vc))
+    assert bool((outs[0][0] != 0).any())
+    assert all(torch.equal(a, b) for a, b in zip(*outs))
