@@ -8,7 +8,8 @@
 // partition by decreasing length; a persistent grid of 4-wave workgroups
 // walks that list in snake order (workgroup w takes items w, 2G - 1 - w,
 // 2G + w, ...), which keeps the workgroups' totals within about one short item
-// of each other. Within an item each wave owns a quarter of the tokens,
+// of each other. Many short items go to single waves instead, in the same order.
+// Within an item each wave owns a quarter of the tokens,
 // processed in chunks of 32 tokens = two 16-token KV blocks, with the next
 // chunk's K/V loads in flight while the current one computes. The query heads of a KV group (up to
 // 16) ride in the MFMA's 16 columns, so every KV byte is read once for all of
@@ -67,6 +68,15 @@ __device__ __forceinline__ int split_len(float mean) {
   return p + p / 2 <= x ? p + p / 2 : p;
 }
 
+// With more items than workgroups and at most this many tokens an item on
+// average, a wave takes an item by itself: four waves on one would each read a
+// few blocks (a wave's share is at least 64 tokens, so the fourth has nothing
+// from 192 tokens down) and then merge. Shared / solo, us a call on the 70B
+// heads: 512 sequences of 16-64 tokens 80 / 40, 256 of 64-128 49 / 35, 100 of
+// 100-300 33 / 29, 512 of 64-1024 220 / 210, 300 of 400-600 124 / 121; but 256
+// of 512-2048 226 / 242, and 16 of 256-512 (128 items) 19 / 26.
+constexpr float kSoloTokens = 576.f;
+
 // Most items a split launch lists, and so the partial records it can need. A
 // length is above 2/3 of its bound, so the full partitions number below 1.5 /
 // kShareLong = 1.2 per workgroup; the sequences' last ones add fewer than 4.
@@ -84,10 +94,12 @@ size_t attn_ws_bytes(int max_batch, int hq, int hkv, int d, int max_seq, int num
   return (size_t)std::min<int64_t>(finest, attn_item_cap(num_cus)) * attn_rec_floats(hq / hkv, d) * sizeof(float);
 }
 
-// The plan: [0] entries listed, [1] partition length, then for each sequence
+// The plan: [0] entries listed, [1] partition length, [2] whether a wave takes
+// an item by itself, then for each sequence
 // the index of its first full partition and of its last, shorter one, then the
 // entries, b | part << 16.
-static int plan_entries(int batch) { return 2 + 2 * batch; }
+constexpr int kPlanHead = 3;
+static int plan_entries(int batch) { return kPlanHead + 2 * batch; }
 
 size_t attn_plan_bytes(int max_batch, int num_cus) {
   return (size_t)(plan_entries(max_batch) + std::max(max_batch, attn_item_cap(num_cus))) * sizeof(int32_t);
@@ -126,16 +138,13 @@ __global__ void __launch_bounds__(256) k_attn_plan(const int32_t* __restrict__ p
     const int n = positions[b] + 1;
     s_seq[b] = n >= 1 && n <= max_tokens ? n : 0;
   }
-  int ptok = kMaxLen;
-  if (!whole) {
-    int sum = 0;
-    for (int b = b0; b < b1; b++) sum += s_seq[b];
-    // in units of 16 tokens: a split launch has fewer than 2048 sequences of at most 2^20 tokens
-    sum = wave_sum_i((sum + 15) / 16);
-    if (lane == 0) s_sum[wave] = sum;
-    __syncthreads();
-    ptok = split_len(16.f * (float)hkv * (float)(s_sum[0] + s_sum[1] + s_sum[2] + s_sum[3]) / (float)G);
-  }
+  int sum = 0;  // in units of 16 tokens: at most 4096 sequences of 2^20 tokens
+  for (int b = b0; b < b1; b++) sum += (s_seq[b] + 15) / 16;
+  sum = wave_sum_i(sum);
+  if (lane == 0) s_sum[wave] = sum;
+  __syncthreads();
+  const float tokens = 16.f * ((float)s_sum[0] + (float)s_sum[1] + (float)s_sum[2] + (float)s_sum[3]);
+  const int ptok = whole ? kMaxLen : split_len(tokens * (float)hkv / (float)G);
   // full partitions of each sequence, their exclusive prefix, and the keys of the short ones
   int local = 0, shorts = 0;
   for (int b = b0; b < b1; b++) {
@@ -159,10 +168,12 @@ __global__ void __launch_bounds__(256) k_attn_plan(const int32_t* __restrict__ p
   int run = incl - local;
   for (int w = 0; w < wave; w++) run += s_scan[w];
   if (blockIdx.x == 0 && t == 0) {
-    plan[0] = nfull + s_short[0] + s_short[1] + s_short[2] + s_short[3];
+    const int listed = nfull + s_short[0] + s_short[1] + s_short[2] + s_short[3];
+    plan[0] = listed;
     plan[1] = ptok;
+    plan[2] = (int64_t)listed * hkv > G && tokens <= kSoloTokens * (float)listed;
   }
-  int32_t* first = plan + 2;
+  int32_t* first = plan + kPlanHead;
   int32_t* last = first + batch;
   int32_t* entries = last + batch;
   const int lo = blockIdx.x * kPlanSeqs, hi = min(batch, lo + kPlanSeqs);
@@ -325,10 +336,11 @@ __device__ __forceinline__ void compute_chunk(const Chunk<D>& c, const bf16x8_t 
 // Item i of the work list is (entry i / Hkv of the plan, KV head i % Hkv).
 // Two 4-wave workgroups per CU; a wave holds 218 VGPRs (224 allocated), so
 // two of them and a slot-fill wave (at most 48) fit in a SIMD's 512.
-template <int D>
-__global__ void __launch_bounds__(256, 2) k_attn(AttnCall a) {
+// SOLO: a wave takes a whole item by itself, so nothing is merged in LDS and the
+// waves of a workgroup go their own ways (no barrier).
+template <int D, bool SOLO>
+__device__ __forceinline__ void run_items(const AttnCall& a, float* smem_f) {
   constexpr int KK = D / 32, JD = D / 16;
-  extern __shared__ __attribute__((aligned(16))) float smem_f[];
   float* s_m = smem_f;                             // [4][16]
   float* s_l = s_m + 64;                           // [4][16]
   float* s_o = s_l + 64;                           // [4][16][D + 1]
@@ -340,7 +352,7 @@ __global__ void __launch_bounds__(256, 2) k_attn(AttnCall a) {
   cint32_t* plan = (cint32_t*)a.plan;
   const int total_items = plan[0] * a.hkv;
   const int part_tokens = plan[1];
-  cint32_t* entries = plan + 2 + 2 * a.batch;
+  cint32_t* entries = plan + kPlanHead + 2 * a.batch;
   const float scale = kLog2e / sqrtf((float)D);
   const int64_t region_blk = (int64_t)a.region * a.kv.nblk;
   cint32_t* positions = (cint32_t*)a.positions;
@@ -363,15 +375,16 @@ __global__ void __launch_bounds__(256, 2) k_attn(AttnCall a) {
     // masked extra chunk re-reads HBM: non-temporal loads leave nothing in L2),
     // so a sequence's shorter last partition keeps all four waves loading
     const int len = min(it.seq - it.part * part_tokens, part_tokens);
-    const int share = ((len + 3) / 4 + 63) / 64 * 64;
-    it.tb = it.part * part_tokens + wave * share;
+    const int share = SOLO ? len : ((len + 3) / 4 + 63) / 64 * 64;
+    it.tb = it.part * part_tokens + (SOLO ? 0 : wave * share);
     it.te = min(it.tb + share, it.part * part_tokens + len);
   };
-  // the r-th item of this workgroup in snake order over the sorted list
-  auto item_of = [&](int r) {
-    const int G = gridDim.x;
-    return (r & 1) ? (r + 1) * G - 1 - (int)blockIdx.x : r * G + (int)blockIdx.x;
-  };
+  // the r-th item of this worker (workgroup, or wave when solo) in snake order
+  // over the sorted list; a workgroup's waves are a grid apart in the list, so
+  // the longest items start on different CUs
+  const int worker = SOLO ? wave * (int)gridDim.x + (int)blockIdx.x : (int)blockIdx.x;
+  const int workers = SOLO ? 4 * (int)gridDim.x : (int)gridDim.x;
+  auto item_of = [&](int r) { return (r & 1) ? (r + 1) * workers - 1 - worker : r * workers + worker; };
   // Query heads ride in the 16 MFMA columns; lanes past the group load a
   // duplicate of the group's first head (finite values whose columns are never
   // merged or written), so the loaded fragments feed the MFMA unmodified and
@@ -454,6 +467,32 @@ __global__ void __launch_bounds__(256, 2) k_attn(AttnCall a) {
 
       l_run += __shfl_xor(l_run, 16, 64);
       l_run += __shfl_xor(l_run, 32, 64);
+      if (SOLO) {
+        // the output rows of a one-partition sequence, else the item's partial
+        // record, straight from the accumulators (four dims of a head each)
+        const bool whole = cur.nparts == 1;
+        const int64_t row0 = (int64_t)cur.b * a.hq + cur.g * group;
+        float* rec = a.part + (whole ? 0 : (int64_t)item * attn_rec_floats(group, D));
+#pragma unroll
+        for (int jd = 0; jd < JD; jd++) {
+          const int d = jd * 16 + lg * 4;
+          if (head >= group) continue;
+          if (whole)
+            *(u32x2_t*)(a.out + (row0 + head) * D + d) =
+                u32x2_t{pack_bf2(o[jd][0] / l_run, o[jd][1] / l_run), pack_bf2(o[jd][2] / l_run, o[jd][3] / l_run)};
+          else
+            *(f32x4_t*)(rec + head * D + d) = o[jd];
+        }
+        if (!whole && lg == 0) {
+          rec[group * D + 2 * head] = head < group ? m_run : 0.f;
+          rec[group * D + 2 * head + 1] = head < group ? l_run : 0.f;
+        }
+        if (!has_next) break;
+        cur = nx;
+        item = nitem;
+        round++;
+        continue;
+      }
       if (lg == 0) {
         s_m[wave * 16 + head] = m_run;
         s_l[wave * 16 + head] = l_run;
@@ -514,6 +553,13 @@ __global__ void __launch_bounds__(256, 2) k_attn(AttnCall a) {
   if (bad && lane == 0) atomicOr(a.err, SIDP_DEVERR_BLOCK);
 }
 
+template <int D>
+__global__ void __launch_bounds__(256, 2) k_attn(AttnCall a) {
+  extern __shared__ __attribute__((aligned(16))) float smem_f[];
+  if (((cint32_t*)a.plan)[2]) run_items<D, true>(a, smem_f);
+  else run_items<D, false>(a, smem_f);
+}
+
 // Log-sum-exp merge of a sequence's partitions: one workgroup per (KV head,
 // sequence) covering the group's query heads, four dims per thread (16-byte
 // loads from the partial records). Partitions are summed in index order. Bound
@@ -532,8 +578,8 @@ __global__ void __launch_bounds__(256) k_attn_combine(AttnCall a) {
   if (nparts <= 1) return;
   const int rf = attn_rec_floats(group, D);
   // records of partitions 0 .. full - 1 are hkv * rf floats apart; the short last one has its own place
-  const float* recs = a.part + ((int64_t)plan[2 + b] * a.hkv + g) * rf;
-  const float* tail = a.part + (nparts > full ? ((int64_t)plan[2 + a.batch + b] * a.hkv + g) * rf : 0);
+  const float* recs = a.part + ((int64_t)plan[kPlanHead + b] * a.hkv + g) * rf;
+  const float* tail = a.part + (nparts > full ? ((int64_t)plan[kPlanHead + a.batch + b] * a.hkv + g) * rf : 0);
   auto rec_of = [&](int j) { return j < full ? recs + (int64_t)j * a.hkv * rf : tail; };
   {
     const int hh = threadIdx.x & 15;  // (m, l) pairs past the group are zero padding

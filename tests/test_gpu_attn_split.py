@@ -26,6 +26,9 @@ def _mixed(n, hi, seed):
     (4, 2, 64, _mixed(300, 2500, 2)),                          # five, per-thread runs of two sequences
     (4, 2, 64, [1] * 70 + [9000] + [2] * 70),                  # one long sequence among short ones
     (2, 1, 64, _mixed(700, 900, 3)),                           # mostly one partition each, past the whole-launch width
+    (64, 8, 128, _mixed(130, 300, 4)),                         # a wave an item, whole sequences, uneven waves
+    (16, 1, 128, _mixed(600, 700, 5)),                         # a wave an item, the largest group
+    (8, 2, 64, _mixed(400, 1000, 6) + [1, 15, 16, 17, 31, 32, 33, 5000]),  # a wave an item, some of them partitions
 ])
 def test_split_attention_parity(lib, hq, hkv, d, seqs):
     cfg = synth.get_config("tiny_layer", num_q_heads=hq, num_kv_heads=hkv, head_dim=d)
