@@ -13,6 +13,9 @@ constexpr int kFragElems = 512;    // 64 lanes x 8 bf16
 
 __host__ __device__ inline int round_up(int a, int b) { return (a + b - 1) / b * b; }
 
+// Packed weights from here on do not stay cached from one reader to the next (k_gemm_deep.hip has the times).
+constexpr size_t kNtBytes = (size_t)150 << 20;
+
 struct GemmArgs {
   const uint16_t* x;   // [M, K] bf16, row stride K
   const uint16_t* w;   // packed

@@ -432,17 +432,20 @@ __global__ void __launch_bounds__(512, 1) k_gemm_lw(GemmArgs a) {
 }
 
 // Sum split-K partials in split order and apply the epilogue. VEC columns per
-// thread (4 with 16-byte loads, where the sizes and pointers allow; else 1), one
-// row per blockIdx.y, eight splits' loads in flight. Bound by the partials' read:
+// thread (4 with 16-byte loads, where the sizes and pointers allow; else 1), eight
+// splits' loads in flight. Outputs are numbered through the rows: with a row per
+// blockIdx.y the stores of rows of odd length began inside a cache line (466 rows
+// of 7193 columns 17.2 us instead of 12.5). Bound by the partials' read:
 // QKV at 256 rows (3 splits, 31 MB) takes 7.4 us; one column a thread, with a
 // 64-bit division for its row, took 10.4.
 template <int EPI, int VEC>
 __global__ void __launch_bounds__(256) k_splitk_reduce(GemmArgs a) {
   typedef float vec_t __attribute__((ext_vector_type(VEC)));
   const int NP = a.NG * 64;
-  const int row = blockIdx.y, c = (blockIdx.x * 256 + threadIdx.x) * VEC;
-  if (c >= a.N) return;
-  const int64_t idx = (int64_t)row * a.N + c;
+  const int64_t idx = ((int64_t)blockIdx.x * 256 + threadIdx.x) * VEC;
+  if (idx >= (int64_t)a.M * a.N) return;
+  const int row = idx >> 32 ? (int)(idx / a.N) : (int)((uint32_t)idx / (uint32_t)a.N);
+  const int c = (int)(idx - (int64_t)row * a.N);
   const int64_t step = (int64_t)a.M * NP;  // from one split's partials to the next's
   const float* p = a.ws + (int64_t)row * NP + (EPI == SIDP_EPI_SWIGLU ? (c / 32) * 64 + (c % 32) : c);
   vec_t v = 0.f, u = 0.f;  // SWIGLU: gate columns and, 32 on, their up columns
@@ -486,8 +489,8 @@ template <int EPI>
 static hipError_t launch_splitk_reduce(const GemmArgs& a, hipStream_t s) {
   const size_t align = EPI == SIDP_EPI_RESID ? 16 : 8;
   const bool vec = a.N % 4 == 0 && (int64_t)a.M * a.N >= kVecOutputs && (uintptr_t)a.out % align == 0 && (uintptr_t)a.resid % 16 == 0;
-  const int cols = vec ? 1024 : 256;  // per workgroup
-  const dim3 grid((a.N + cols - 1) / cols, a.M);
+  const int64_t outs = (int64_t)a.M * a.N, each = vec ? 1024 : 256;  // outputs per workgroup
+  const unsigned grid = (unsigned)((outs + each - 1) / each);
   if (vec) k_splitk_reduce<EPI, 4><<<grid, 256, 0, s>>>(a);
   else k_splitk_reduce<EPI, 1><<<grid, 256, 0, s>>>(a);
   return hipGetLastError();
@@ -690,10 +693,15 @@ hipError_t launch_linear(const LinearCall& c, hipStream_t s) {
   // 8 a wide unsplit k_gemm, 0 the 4-wave k_gemm
   const GemmPlan plan = plan_linear(c.m, c.n, c.k, c.epilogue, c.num_cus);
   const int wide = plan.kernel == 1 ? -1 : plan.waves > kWaves ? plan.waves : 0;
-  // Alone on the chip the deep pipeline is the faster form of kernel 0 at every
-  // size measured; beside a slot fill the shallow one is (both sides' times in
-  // k_gemm_deep.hip). Its direct-to-LDS loads need 16-byte aligned activations.
-  const bool deep = plan.kernel == 0 && !c.beside_fill && (uintptr_t)c.x % 16 == 0;
+  // Alone on the chip the deep pipeline is the faster form of kernel 0 except
+  // where a second row block of at most 32 rows shares weights too large to stay
+  // cached (kernel alone, us, k_gemm / deep: 470 MB at 129, 145, 160, 192 rows 219 /
+  // 236, 208 / 228, 220 / 227, 225 / 223; 484 MB 130 / 149, 130 / 143, 128 / 136,
+  // 127 / 112; 168 MB 49 / 52, 49 / 49, 49 / 45). Beside a slot fill the shallow
+  // one is faster (both sides' times in k_gemm_deep.hip). The deep one's
+  // direct-to-LDS loads need 16-byte aligned activations.
+  const bool thin_block = c.m > 128 && c.m <= 160 && (size_t)a.NG * 64 * a.KP * 2 >= kNtBytes;
+  const bool deep = plan.kernel == 0 && !c.beside_fill && !thin_block && (uintptr_t)c.x % 16 == 0;
   hipError_t e;
   if (a.splits == 1) {
     if (deep) e = launch_gemm_deep(a, c.epilogue, plan.rows, plan.waves, s);

@@ -37,8 +37,11 @@ namespace sidp {
 // 64, 128, 256 rows 50.7 / 46.4, 56.0 / 53.1, 66.1 / 62.6, 93.2 / 89.9; 470 MB at
 // 100 rows 97 / 89; 940 MB at 100 rows 156 / 146, at 512 (four row blocks) 404 /
 // 400; but 134 MB at 64 rows 35.1 / 38.1 and 105 MB 28.9 / 31.6.
-constexpr size_t kNtBytes = (size_t)150 << 20;
-constexpr int kNtRowBlocks = 4;
+// And only where no row block is ragged: the workgroups of a part-filled last
+// block load fewer activations and run ahead of their pair, whose weights then
+// come from HBM again (kernel alone, us, cached / non-temporal): 470 MB at 135 rows
+// 209 / 228, at 300 346 / 353; 484 MB at 135 135 / 155; 206 MB at 200 62 / 67.
+constexpr int kNtRowBlocks = 4;  // kNtBytes is in gemm.h
 
 // One workgroup: W waves (4, or 7 or 8 for wide unsplit launches). Wave wn
 // computes rows [row0, row0 + MF*32) x the 64 packed columns of group
@@ -238,7 +241,7 @@ static hipError_t launch_w(GemmArgs a, hipStream_t s) {
   a.mblocks = (a.M + MF * 32 - 1) / (MF * 32);
   a.tiles = (a.NG + W - 1) / W;
   const int grid = (a.tiles * a.splits + 7) / 8 * 8 * a.mblocks;
-  const bool nt = (size_t)a.NG * 64 * a.KP * 2 >= kNtBytes && a.mblocks <= kNtRowBlocks;
+  const bool nt = (size_t)a.NG * 64 * a.KP * 2 >= kNtBytes && (a.mblocks == 1 || (a.mblocks <= kNtRowBlocks && a.M % (MF * 32) == 0));
   if (nt) k_gemm_deep<MF, EPI, P, W, true><<<grid, 64 * W, 0, s>>>(a);
   else k_gemm_deep<MF, EPI, P, W, false><<<grid, 64 * W, 0, s>>>(a);
   return hipGetLastError();

@@ -60,7 +60,9 @@ def test_every_depth_and_row_block(lib, m):
 
 
 @pytest.mark.parametrize("m,n,k,epi", [(200, 28672, 520, 2), (129, 29568, 1032, 2), (260, 28672, 64, 2),
-                                       (200, 45056, 264, 0), (512, 28672, 584, 1), (200, 8192, 25608, 1)])
+                                       (200, 45056, 264, 0), (512, 28672, 584, 1), (200, 8192, 25608, 1),
+                                       # 158 MB of weights: ragged, whole and nearly empty second row blocks
+                                       (161, 8192, 9672, 1), (256, 8192, 9672, 1), (129, 8192, 9672, 1), (160, 8192, 9672, 1)])
 def test_wide_workgroups_and_large_weights(lib, m, n, k, epi):
     _check(lib, m, n, k, epi, _x(m, k))
 
