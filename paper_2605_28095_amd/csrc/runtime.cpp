@@ -213,7 +213,6 @@ struct sidp_handle {
   // its weights; 0: the layer waits for its whole fill before it starts
   int part_waits = 1;
   int step_batch = 0;  // rows of the decode step being issued
-  bool step_streamed = false;  // a streamed decode step is being issued: its projections run beside slot fills
   // pooling: which part of a layer is staged, and which layers this rank owns
   int pool_mode = SIDP_POOL_LAYER;
   int ranks = 0, rank = 0;          // layer l is owned (never staged) when ranks > 0 and l % ranks == rank
@@ -536,7 +535,6 @@ static LinearCall linear_call(const sidp_handle* h, const void* x, int m, int k,
   c.ws = h->ws;
   c.ws_bytes = h->ws_bytes;
   c.num_cus = h->num_cus;
-  c.beside_fill = h->step_streamed;
   return c;
 }
 
@@ -582,9 +580,10 @@ static hipError_t time_end(sidp_handle* h, int cls, hipStream_t s) {
   } while (0)
 
 // The attention half of a layer (norm, QKV, QK-norm/RoPE/KV append,
-// attention), reading weights from `wb` (a pool blob or a slot).
+// attention), reading weights from `wb` (a pool blob or a slot). beside_fill: the
+// step is streamed, so slot fills run beside its projections.
 static hipError_t run_attn_half(sidp_handle* h, const uint8_t* wb, int layer, float* hidden, const int32_t* positions,
-                                const int32_t* bt, int max_blocks, int B, hipStream_t s) {
+                                const int32_t* bt, int max_blocks, int B, bool beside_fill, hipStream_t s) {
   const sidp_config& c = h->cfg;
   const BlobLayout& L = h->blob;
   const int H = c.hidden, D = c.head_dim;
@@ -596,6 +595,7 @@ static hipError_t run_attn_half(sidp_handle* h, const uint8_t* wb, int layer, fl
   const uint16_t* qkv_bias = c.qkv_bias ? (const uint16_t*)(wb + L.bias) : nullptr;
   LinearCall qc = linear_call(h, h->h, B, H, wb + L.w_qkv, qkv_rows(c), SIDP_EPI_BF16, qkv_bias, nullptr, h->qkv);
   qc.defer_reduce = true;
+  qc.beside_fill = beside_fill;
   const int qkv_splits = gemm_splits(B, qkv_rows(c), H, h->num_cus);
   TIMED(h, SIDP_K_QKV, s, launch_linear(qc, s));
   // a4/a5: QK-norm, RoPE, KV append at the slot of each sequence's position
@@ -675,7 +675,7 @@ static hipError_t wait_slot_bytes(SlotWaits* w, size_t need_end, hipStream_t s) 
 // `wa` holds the layer's attention part (W_o), `wf` its FFN part; both are
 // the same blob unless only the FFN part is staged.
 static hipError_t run_proj_half(sidp_handle* h, const uint8_t* wa, const uint8_t* wf, int layer, float* hidden, int B,
-                                hipStream_t s, SlotWaits* waits = nullptr) {
+                                bool beside_fill, hipStream_t s, SlotWaits* waits = nullptr) {
   const sidp_config& c = h->cfg;
   const BlobLayout& L = h->blob;
   const int H = c.hidden, QD = c.num_q_heads * c.head_dim;
@@ -688,17 +688,19 @@ static hipError_t run_proj_half(sidp_handle* h, const uint8_t* wa, const uint8_t
   oc.norm_gain = wf + L.g_mlp;
   oc.norm_eps = c.rms_eps;
   oc.norm_out = h->h;
+  oc.beside_fill = beside_fill;
   TIMED(h, SIDP_K_O, s, launch_linear(oc, s));
   // a9: gate/up projection + SwiGLU; the FFN's weights (gate/up, then down)
   // take one wait, for the whole fill: a second wait inside the FFN gained
   // nothing measurable and its timing brackets cost about 1 ms per step
   if ((e = wait_slot_bytes(waits, L.total, s)) != hipSuccess) return e;
-  TIMED(h, SIDP_K_GATE_UP, s,
-        launch_linear(linear_call(h, h->h, B, H, wf + L.w_gu, c.ffn_dim, SIDP_EPI_SWIGLU, nullptr, nullptr, h->act),
-                      s));
+  LinearCall gc = linear_call(h, h->h, B, H, wf + L.w_gu, c.ffn_dim, SIDP_EPI_SWIGLU, nullptr, nullptr, h->act);
+  gc.beside_fill = beside_fill;
+  TIMED(h, SIDP_K_GATE_UP, s, launch_linear(gc, s));
   // a10: down projection + residual, fused with the next layer's attention
   // norm (a2 of layer + 1) when there is a next layer in this step
   LinearCall dc = linear_call(h, h->act, B, c.ffn_dim, wf + L.w_d, H, SIDP_EPI_RESID, nullptr, hidden, hidden);
+  dc.beside_fill = beside_fill;
   if (layer + 1 < c.num_layers) {
     dc.norm_gain = h->g_attn_all + (size_t)(layer + 1) * H;
     dc.norm_eps = c.rms_eps;
@@ -709,10 +711,10 @@ static hipError_t run_proj_half(sidp_handle* h, const uint8_t* wa, const uint8_t
 }
 
 static hipError_t run_layer(sidp_handle* h, const uint8_t* wb, int layer, float* hidden, const int32_t* positions,
-                            const int32_t* bt, int max_blocks, int B, hipStream_t s) {
-  hipError_t e = run_attn_half(h, wb, layer, hidden, positions, bt, max_blocks, B, s);
+                            const int32_t* bt, int max_blocks, int B, bool beside_fill, hipStream_t s) {
+  hipError_t e = run_attn_half(h, wb, layer, hidden, positions, bt, max_blocks, B, beside_fill, s);
   if (e != hipSuccess) return e;
-  return run_proj_half(h, wb, wb, layer, hidden, B, s);
+  return run_proj_half(h, wb, wb, layer, hidden, B, beside_fill, s);
 }
 
 // The staged byte range [lo, hi) of a layer blob and the end `mid` of fill part A.
@@ -780,7 +782,6 @@ int sidp_decode_step(sidp_handle* h, float* hidden, const int32_t* positions, co
   const bool streamed = flags & SIDP_STREAMED;
   h->timing = (flags & SIDP_TIMING) != 0;
   h->step_batch = batch;
-  h->step_streamed = streamed;
   hipStream_t cs = (hipStream_t)compute, cp = (hipStream_t)copy;
   if (streamed && (!h->slots || cp == cs)) return SIDP_EINVAL;
   HIPCHK(h, begin_call(h, cs));
@@ -801,7 +802,7 @@ int sidp_decode_step(sidp_handle* h, float* hidden, const int32_t* positions, co
   if (!streamed) {
     for (int l = 0; l < c.num_layers; l++)
       HIPCHK(h, run_layer(h, h->pool + (size_t)l * h->blob.total, l, hidden, positions, block_tables,
-                          max_blocks_per_seq, batch, cs));
+                          max_blocks_per_seq, batch, false, cs));
     HIPCHK(h, finish_call(h, cs));
     return SIDP_OK;
   }
@@ -839,13 +840,13 @@ int sidp_decode_step(sidp_handle* h, float* hidden, const int32_t* positions, co
         break;
       case OP_ATTN:
         HIPCHK(h, run_attn_half(h, ffn_only ? own : slot, layer, hidden, positions, block_tables, max_blocks_per_seq,
-                                batch, cs));
+                                batch, true, cs));
         break;
       case OP_MID:
         HIPCHK(h, hipEventRecord(h->mid[op.slot], cs));
         break;
       case OP_PROJ:
-        HIPCHK(h, run_proj_half(h, ffn_only ? own : slot, slot, layer, hidden, batch, cs, &waits));
+        HIPCHK(h, run_proj_half(h, ffn_only ? own : slot, slot, layer, hidden, batch, true, cs, &waits));
         break;
       case OP_DONE:
         HIPCHK(h, hipEventRecord(h->consumed[op.slot], cs));
@@ -857,12 +858,11 @@ int sidp_decode_step(sidp_handle* h, float* hidden, const int32_t* positions, co
         HIPCHK(h, hipStreamWaitEvent(cp, h->mid[op.slot], 0));
         break;
       case OP_LOCAL:
-        HIPCHK(h, run_layer(h, own, layer, hidden, positions, block_tables, max_blocks_per_seq, batch, cs));
+        HIPCHK(h, run_layer(h, own, layer, hidden, positions, block_tables, max_blocks_per_seq, batch, true, cs));
         break;
     }
   }
   HIPCHK(h, finish_call(h, cs));
-  h->step_streamed = false;
   return SIDP_OK;
 }
 

@@ -174,3 +174,14 @@ class Stack:
 
     def close(self):
         self.dec.close()
+
+
+def kernels_of(call):
+    """Names of the GPU kernels that `call` launches, in launch order."""
+    from torch.profiler import ProfilerActivity, profile
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CUDA], acc_events=True) as prof:
+        call()
+        torch.cuda.synchronize()
+    return [e.name for e in sorted(prof.events(), key=lambda e: e.time_range.start)
+            if e.device_type == torch.autograd.DeviceType.CUDA]

@@ -25,7 +25,7 @@ import torch
 
 import oracle
 import synth
-from gpu_helpers import Stack, assert_bf16_within_ulp, bits, row_rel_err
+from gpu_helpers import Stack, assert_bf16_within_ulp, bits, kernels_of, row_rel_err
 
 pytestmark = pytest.mark.gpu
 
@@ -273,6 +273,39 @@ def test_step_error_paths(lib):
             st.dec.sync()
         assert e.value.code == E
         st.dec.sync()  # the latch is cleared
+    finally:
+        st.close()
+
+
+def test_refused_streamed_step_leaves_single_calls_on_the_deep_pipeline(lib):
+    """The shallow projection kernel belongs to streamed steps only: a streamed
+    step that is refused, or one that has run, leaves sidp_linear on k_gemm_deep."""
+    cfg = synth.get_config("tiny_layer")
+    st = Stack(cfg)
+    try:
+        n, k, dev = 512, 256, "cuda"
+        w = torch.randn(n, k, device=dev).to(torch.bfloat16)
+        packed = torch.empty(lib.sidp_packed_bytes(n, k), dtype=torch.uint8, device=dev)
+        lib.sidp_pack_linear(w, n, k, packed)
+        x = torch.randn(st.batch, k, device=dev).to(torch.bfloat16)
+        out = torch.empty(st.batch, n, dtype=torch.bfloat16, device=dev)
+
+        def linear():
+            lib.sidp_linear(st.dec.h, x, st.batch, k, packed, n, lib.SIDP_EPI_BF16, None, None, out)
+
+        def kernel():
+            return next(name for name in kernels_of(linear) if "k_gemm" in name)
+
+        assert "k_gemm_deep" in kernel()
+        s = torch.cuda.current_stream().cuda_stream
+        assert lib.raw_call("sidp_decode_step", st.dec.h, st.hidden.data_ptr(), st.positions.data_ptr(),
+                            st.bt.data_ptr(), st.bt.shape[1], st.batch, lib.SIDP_STREAMED, s, s) == lib.SIDP_EINVAL
+        assert "k_gemm_deep" in kernel()
+        copy = torch.cuda.Stream()
+        ran = kernels_of(lambda: st.dec.step(st.hidden, st.positions, st.bt, lib.SIDP_STREAMED, copy=copy))
+        assert any("k_gemm" in name for name in ran) and not any("k_gemm_deep" in name for name in ran)
+        assert "k_gemm_deep" in kernel()
+        st.dec.sync()
     finally:
         st.close()
 
