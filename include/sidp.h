@@ -399,6 +399,21 @@ int sidp_linear_plan(int32_t m, int32_t n, int32_t k, int32_t epilogue, int32_t 
                      int32_t *waves, int32_t *rows_per_workgroup, int32_t *splits, int32_t *workgroups,
                      uint64_t *ws_bytes);
 
+/* How sidp_attention and the decode step cut the attention over `batch`
+ * sequences at `positions` (HOST memory here) with block tables of
+ * max_blocks_per_seq 16-token blocks, on a GPU with `num_cus` compute units
+ * (host only, no device call). part_tokens: the longest piece of a sequence
+ * that one item covers (2^20 where sequences are left whole). items:
+ * (sequence, piece, KV head) triples. wave_items: 1 where each wave takes an
+ * item by itself, 0 where a workgroup's four waves share one. combine: 1 where
+ * a second launch merges the pieces. All depend on every sequence's length, so
+ * the fp32 grouping of one sequence's sums, and with it the last bits of its
+ * output, can change with the other sequences of the batch. All outputs host,
+ * caller-owned. SIDP_EINVAL for a null pointer, batch outside 1..4096,
+ * num_kv_heads or num_cus < 1, or tables past 2^20 tokens. */
+int sidp_attention_plan(const int32_t *positions, int32_t batch, int32_t max_blocks_per_seq, int32_t num_kv_heads,
+                        int32_t num_cus, int32_t *part_tokens, int32_t *items, int32_t *wave_items, int32_t *combine);
+
 /* Bytes of a matrix [n, k] packed for sidp_linear (n padded to 64, k to 64). */
 size_t sidp_packed_bytes(int32_t n, int32_t k);
 /* Packs W (device bf16 [n, k], nn.Linear layout) into `packed`

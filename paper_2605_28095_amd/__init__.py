@@ -54,6 +54,7 @@ EXPORTED = [
     "sidp_pack_gate_up", "sidp_linear", "sidp_slot_mapping", "sidp_rope_append", "sidp_attention", "sidp_copy",
     "sidp_timing_collect", "sidp_set_pooling", "sidp_cas_ffn", "sidp_timing_select", "sidp_mode_update",
     "sidp_set_fill_tiles", "sidp_debug_inject_hip_error", "sidp_linear_noalloc", "sidp_linear_plan",
+    "sidp_attention_plan",
 ]
 
 SIDP_CAS_MAX_REPLICAS = 16
@@ -133,6 +134,7 @@ _sigs = {
     "sidp_linear_noalloc": (ctypes.c_int, [_P, _I, _I, _P, _I, _I, _P, _P, _P, _P]),
     "sidp_linear_plan": (ctypes.c_int, [_I, _I, _I, _I, _I, _PI, _PI, _PI, _PI, _PI,
                                         ctypes.POINTER(ctypes.c_uint64)]),
+    "sidp_attention_plan": (ctypes.c_int, [_PI, _I, _I, _I, _I, _PI, _PI, _PI, _PI]),
     "sidp_slot_mapping": (ctypes.c_int, [_P, _P, _P, _I, _I, _P, _P]),
     "sidp_rope_append": (ctypes.c_int, [_P, _P, _P, _P, _I, _I, _P, _P, _I, _P, _P]),
     "sidp_attention": (ctypes.c_int, [_P, _P, _I, _P, _P, _I, _I, _P, _P]),
@@ -282,6 +284,16 @@ def sidp_linear_plan(m, n, k, epilogue, num_cus=256):
            "sidp_linear_plan")
     names = ("kernel", "waves", "rows", "splits", "workgroups")
     return dict({nm: o.value for nm, o in zip(names, out)}, ws_bytes=ws.value)
+
+
+def sidp_attention_plan(positions, max_blocks_per_seq, num_kv_heads, num_cus=256):
+    """How the attention over sequences at `positions` is cut (host only):
+    part_tokens, items, wave_items and combine."""
+    pos = (ctypes.c_int32 * len(positions))(*[int(p) for p in positions])
+    out = [ctypes.c_int32() for _ in range(4)]
+    _check(_lib.sidp_attention_plan(pos, len(positions), max_blocks_per_seq, num_kv_heads, num_cus,
+                                    *[ctypes.byref(o) for o in out]), "sidp_attention_plan")
+    return {nm: o.value for nm, o in zip(("part_tokens", "items", "wave_items", "combine"), out)}
 
 
 def sidp_peak_shift_plan(num_layers, ranks, rank):

@@ -103,6 +103,14 @@ struct AttnCall {
 };
 size_t attn_ws_bytes(int max_batch, int hq, int hkv, int d, int max_seq, int num_cus);
 size_t attn_plan_bytes(int max_batch, int num_cus);
+// What k_attn_plan and launch_attention make of these positions (host memory).
+struct AttnPlan {
+  int part_tokens;  // partition length; 2^20 where sequences stay whole
+  int items;        // (sequence, partition, KV head)
+  bool wave_items;  // a wave takes an item by itself
+  bool combine;     // partial records and the combine kernel
+};
+AttnPlan plan_attention(const int32_t* positions, int batch, int max_tokens, int hkv, int num_cus);
 // Builds the work list from positions; needed once per set of positions (a
 // decode step shares it across its layers). Reads positions, batch, hkv,
 // num_cus, max_blocks, kv.bs, plan, err.

@@ -39,9 +39,11 @@ constexpr float kLog2e = 1.4426950408889634f;
 // which one workgroup reads in about the time the combine's launch takes (16
 // sequences of 256-512 tokens: 20.0 us whole, 21.6 split).
 constexpr int kWholeTokens = 768;
+static bool attn_whole(int batch, int hkv, int max_tokens, int num_cus) {
+  return max_tokens <= kWholeTokens || (int64_t)batch * hkv >= 4 * 2 * (int64_t)std::max(num_cus, 1);
+}
 static bool attn_whole(const AttnCall& c) {
-  return c.max_blocks * c.kv.bs <= kWholeTokens ||
-         (int64_t)c.batch * c.hkv >= 4 * 2 * (int64_t)std::max(c.num_cus, 1);
+  return attn_whole(c.batch, c.hkv, c.max_blocks * c.kv.bs, c.num_cus);
 }
 
 // Partition length of a split launch whose positions leave `mean` tokens of one
@@ -61,10 +63,10 @@ constexpr int kMinLen = 256;
 constexpr float kShare = 2.7f, kShareLong = 1.3f, kLongMean = 1500.f;
 constexpr int kMaxLen = 1 << 20;  // no sequence is longer
 
-__device__ __forceinline__ int split_len(float mean) {
+__host__ __device__ inline int split_len(float mean) {
   const int x = (int)fminf(mean * (mean < kLongMean ? kShare : kShareLong), (float)kMaxLen);
   if (x <= kMinLen) return kMinLen;
-  const int p = 1 << (31 - __builtin_clz(x));
+  const int p = 1 << (31 - __builtin_clz((unsigned)x));
   return p + p / 2 <= x ? p + p / 2 : p;
 }
 
@@ -75,7 +77,18 @@ __device__ __forceinline__ int split_len(float mean) {
 // heads: 512 sequences of 16-64 tokens 80 / 40, 256 of 64-128 49 / 35, 100 of
 // 100-300 33 / 29, 512 of 64-1024 220 / 210, 300 of 400-600 124 / 121; but 256
 // of 512-2048 226 / 242, and 16 of 256-512 (128 items) 19 / 26.
+// And only while the longest item has at most kSoloLongest tokens for each item
+// that a workgroup would take: a lone wave walks it serially, in about the time
+// a workgroup needs for one short item per 256 tokens, and the launch ends with
+// it. Shared / solo: 256 sequences of 16-64 tokens (4 items a workgroup) 41.7 /
+// 22.1, one of them of 512 44.6 / 33.5, 1023 45.4 / 44.6, 1500 49.6 / 59.3, 8190
+// 114 / 241; 512 of 64-512 (8 items a workgroup), one of them of 2000 147.5 /
+// 144.2, 3000 155 / 171, 8190 209 / 311.
 constexpr float kSoloTokens = 576.f;
+constexpr int kSoloLongest = 256;
+__host__ __device__ inline bool attn_solo(int64_t items, float mean_tokens, int longest, int G) {
+  return items > G && mean_tokens <= kSoloTokens && (int64_t)longest * G <= kSoloLongest * items;
+}
 
 // Most items a split launch lists, and so the partial records it can need. A
 // length is above 2/3 of its bound, so the full partitions number below 1.5 /
@@ -111,6 +124,12 @@ __device__ __forceinline__ int wave_sum_i(int v) {
   return v;
 }
 
+__device__ __forceinline__ int wave_max_i(int v) {
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) v = max(v, __shfl_xor(v, o, 64));
+  return v;
+}
+
 // Writes the plan. Full partitions come first, in (b, part) order; then the
 // last, shorter partition of every sequence that has one, by decreasing length
 // and then increasing b. Positions outside a sequence's block table give no
@@ -127,6 +146,7 @@ __global__ void __launch_bounds__(256) k_attn_plan(const int32_t* __restrict__ p
   // [batch rounded up to 16] each: keys (length << 12 | 4095 - b) of the short partitions, tokens of the sequences
   extern __shared__ __attribute__((aligned(16))) uint32_t s_key[];
   __shared__ int s_sum[4];
+  __shared__ int s_longest[4];
   __shared__ int s_scan[4];
   __shared__ int s_short[4];
   const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
@@ -138,12 +158,19 @@ __global__ void __launch_bounds__(256) k_attn_plan(const int32_t* __restrict__ p
     const int n = positions[b] + 1;
     s_seq[b] = n >= 1 && n <= max_tokens ? n : 0;
   }
-  int sum = 0;  // in units of 16 tokens: at most 4096 sequences of 2^20 tokens
-  for (int b = b0; b < b1; b++) sum += (s_seq[b] + 15) / 16;
+  int sum = 0, longest = 0;  // the sum in units of 16 tokens: at most 4096 sequences of 2^20 tokens
+  for (int b = b0; b < b1; b++) {
+    sum += (s_seq[b] + 15) / 16;
+    longest = max(longest, s_seq[b]);
+  }
   sum = wave_sum_i(sum);
-  if (lane == 0) s_sum[wave] = sum;
+  longest = wave_max_i(longest);
+  if (lane == 0) {
+    s_sum[wave] = sum;
+    s_longest[wave] = longest;
+  }
   __syncthreads();
-  const float tokens = 16.f * ((float)s_sum[0] + (float)s_sum[1] + (float)s_sum[2] + (float)s_sum[3]);
+  const float tokens = 16.f * (float)(s_sum[0] + s_sum[1] + s_sum[2] + s_sum[3]);
   const int ptok = whole ? kMaxLen : split_len(tokens * (float)hkv / (float)G);
   // full partitions of each sequence, their exclusive prefix, and the keys of the short ones
   int local = 0, shorts = 0;
@@ -171,7 +198,8 @@ __global__ void __launch_bounds__(256) k_attn_plan(const int32_t* __restrict__ p
     const int listed = nfull + s_short[0] + s_short[1] + s_short[2] + s_short[3];
     plan[0] = listed;
     plan[1] = ptok;
-    plan[2] = (int64_t)listed * hkv > G && tokens <= kSoloTokens * (float)listed;
+    longest = max(max(s_longest[0], s_longest[1]), max(s_longest[2], s_longest[3]));
+    plan[2] = attn_solo((int64_t)listed * hkv, tokens / (float)max(listed, 1), min(longest, ptok), G);
   }
   int32_t* first = plan + kPlanHead;
   int32_t* last = first + batch;
@@ -620,6 +648,28 @@ __global__ void __launch_bounds__(256) k_attn_combine(AttnCall a) {
     *(uint32_t*)o = pack_bf2(O[0] / L, O[1] / L);
     *(uint32_t*)(o + 2) = pack_bf2(O[2] / L, O[3] / L);
   }
+}
+
+AttnPlan plan_attention(const int32_t* positions, int batch, int max_tokens, int hkv, int num_cus) {
+  const int G = 2 * num_cus;
+  auto tokens_of = [&](int b) {  // as k_attn_plan: none for a position outside its block table
+    const int64_t n = (int64_t)positions[b] + 1;
+    return n >= 1 && n <= max_tokens ? (int)n : 0;
+  };
+  int sum = 0, longest = 0;
+  for (int b = 0; b < batch; b++) {
+    sum += (tokens_of(b) + 15) / 16;
+    longest = std::max(longest, tokens_of(b));
+  }
+  const float tokens = 16.f * (float)sum;
+  AttnPlan p;
+  p.combine = !attn_whole(batch, hkv, max_tokens, num_cus);
+  p.part_tokens = p.combine ? split_len(tokens * (float)hkv / (float)G) : kMaxLen;
+  int listed = 0;
+  for (int b = 0; b < batch; b++) listed += (tokens_of(b) + p.part_tokens - 1) / p.part_tokens;
+  p.items = listed * hkv;
+  p.wave_items = attn_solo(p.items, tokens / (float)std::max(listed, 1), std::min(longest, p.part_tokens), G);
+  return p;
 }
 
 hipError_t launch_attn_plan(const AttnCall& c, hipStream_t s) {

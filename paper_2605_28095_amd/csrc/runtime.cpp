@@ -1108,6 +1108,20 @@ int sidp_linear_plan(int32_t m, int32_t n, int32_t k, int32_t epilogue, int32_t 
   return SIDP_OK;
 }
 
+int sidp_attention_plan(const int32_t* positions, int32_t batch, int32_t max_blocks_per_seq, int32_t num_kv_heads,
+                        int32_t num_cus, int32_t* part_tokens, int32_t* items, int32_t* wave_items, int32_t* combine) {
+  if (!positions || !part_tokens || !items || !wave_items || !combine) return SIDP_EINVAL;
+  if (batch < 1 || batch > 4096 || num_kv_heads < 1 || num_kv_heads > (1 << 16) || num_cus < 1 || num_cus > (1 << 16))
+    return SIDP_EINVAL;
+  if (max_blocks_per_seq < 1 || max_blocks_per_seq > (1 << 20) / 16) return SIDP_EINVAL;
+  const AttnPlan p = plan_attention(positions, batch, max_blocks_per_seq * 16, num_kv_heads, num_cus);
+  *part_tokens = p.part_tokens;
+  *items = p.items;
+  *wave_items = p.wave_items;
+  *combine = p.combine;
+  return SIDP_OK;
+}
+
 int sidp_slot_mapping(sidp_handle* h, const int32_t* positions, const int32_t* block_tables,
                       int32_t max_blocks_per_seq, int32_t batch, int32_t* slots, void* stream) {
   if (!h || !positions || !block_tables || !slots || batch < 0 || max_blocks_per_seq < 1) return SIDP_EINVAL;

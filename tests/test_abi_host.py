@@ -262,3 +262,44 @@ def test_linear_plan_rejects_bad_arguments():
                 (256, 8192, 8192, 3, 256), (256, 8192, 8192, 1, 0), (4, 1 << 21, 1 << 12, 0, 256)]:
         assert sidp.raw_call("sidp_linear_plan", *bad, *refs) == E, bad
     assert sidp.raw_call("sidp_linear_plan", *ok, *refs[:-1], None) == E
+
+
+def _attention_plan(seqs, hkv=8):
+    import paper_2605_28095_amd as sidp
+    return sidp.sidp_attention_plan([s - 1 for s in seqs], -(-max(seqs) // 16), hkv)
+
+
+def test_attention_gives_a_wave_an_item_only_while_no_item_is_long():
+    """A lone wave walks an item serially, so one long sequence among many short
+    ones keeps the four waves of a workgroup together, with whole sequences
+    (the item is the sequence) and with partitions (no longer than those)."""
+    rng = np.random.default_rng(3)
+    for n, hi in [(256, 64), (512, 64), (256, 512), (2048, 300)]:
+        short = rng.integers(hi // 4, hi + 1, n).tolist()
+        assert _attention_plan(short)["wave_items"] == 1
+        for long in (4000, 8192):
+            p = _attention_plan(short[:-1] + [long])
+            assert p["combine"] == 0 and p["part_tokens"] == 1 << 20
+            # longest * workgroups <= 256 * items
+            assert p["wave_items"] == int(long * 512 <= 256 * p["items"]), (n, hi, long)
+    assert _attention_plan([64] * 255 + [1024])["wave_items"] == 1
+    assert _attention_plan([64] * 255 + [1025])["wave_items"] == 0
+    # partitions: no item is longer than one
+    p = _attention_plan([64] * 200 + [8192])
+    assert (p["combine"], p["part_tokens"], p["wave_items"]) == (1, 768, 1)
+    p = _attention_plan([64] * 100 + [8192])
+    assert (p["combine"], p["part_tokens"], p["wave_items"]) == (1, 512, 0)
+
+
+def test_attention_plan_skips_positions_outside_their_table_and_rejects_bad_arguments():
+    import paper_2605_28095_amd as sidp
+    assert sidp.sidp_attention_plan([-1, 31, 32, 2 ** 31 - 1], 2, 8)["items"] == 8
+    E = sidp.SIDP_EINVAL
+    pos = (ctypes.c_int32 * 2)(5, 6)
+    out = [ctypes.c_int32() for _ in range(4)]
+    refs = [ctypes.byref(o) for o in out]
+    assert sidp.raw_call("sidp_attention_plan", pos, 2, 1, 8, 256, *refs) == 0
+    for bad in [(None, 2, 1, 8, 256), (pos, 0, 1, 8, 256), (pos, 4097, 1, 8, 256), (pos, 2, 0, 8, 256),
+                (pos, 2, (1 << 16) + 1, 8, 256), (pos, 2, 1, 0, 256), (pos, 2, 1, 8, 0)]:
+        assert sidp.raw_call("sidp_attention_plan", *bad, *refs) == E, bad
+    assert sidp.raw_call("sidp_attention_plan", pos, 2, 1, 8, 256, *refs[:-1], None) == E

@@ -29,6 +29,9 @@ def _mixed(n, hi, seed):
     (64, 8, 128, _mixed(130, 300, 4)),                         # a wave an item, whole sequences, uneven waves
     (16, 1, 128, _mixed(600, 700, 5)),                         # a wave an item, the largest group
     (8, 2, 64, _mixed(400, 1000, 6) + [1, 15, 16, 17, 31, 32, 33, 5000]),  # a wave an item, some of them partitions
+    (64, 8, 128, _mixed(255, 64, 7) + [8192]),                 # whole sequences, one long among 255 short
+    (16, 8, 64, [40] * 255 + [1024]),                          # the longest sequence that a lone wave takes there
+    (16, 8, 64, [40] * 255 + [1025]),                          # and one token more
 ])
 def test_split_attention_parity(lib, hq, hkv, d, seqs):
     cfg = synth.get_config("tiny_layer", num_q_heads=hq, num_kv_heads=hkv, head_dim=d)
