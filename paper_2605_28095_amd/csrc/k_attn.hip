@@ -37,10 +37,21 @@ constexpr float kLog2e = 1.4426950408889634f;
 // slow it by more than their bytes, so whole sequences win as long as the
 // workgroups stay balanced. And when no sequence can be longer than kWholeTokens,
 // which one workgroup reads in about the time the combine's launch takes (16
-// sequences of 256-512 tokens: 20.0 us whole, 21.6 split).
+// sequences of 256-512 tokens: 20.0 us whole, 21.6 split). Nor, up to
+// kWholeTable tokens, from 3 items for 16 workgroups on while a table has at
+// most kWholeShare tokens for each item that a workgroup would take: there the
+// second launch costs more than shorter items save. Whole / split, us a call on
+// the 70B heads: 12 sequences (96 items) of 900-1100 tokens 23.1 / 24.9, of
+// 1024-1535 26.8 / 26.4; 16 of 900-1100 23.9 / 27.2, of 1024-2040 33.0 / 30.5; 20
+// of 1800-2047 36.0 / 42.3; 24 of 1500 32.3 / 39.2, of 64-2047 31.6 / 30.2; 128
+// of 1024-2040 136.8 / 138.8; but 8 of 512-1023 20.7 / 18.1, 10 of 1500 27.2 / 22.9.
 constexpr int kWholeTokens = 768;
+constexpr int kWholeTable = 2048;
+constexpr int kWholeShare = 6656;
 static bool attn_whole(int batch, int hkv, int max_tokens, int num_cus) {
-  return max_tokens <= kWholeTokens || (int64_t)batch * hkv >= 4 * 2 * (int64_t)std::max(num_cus, 1);
+  const int64_t items = (int64_t)batch * hkv, G = 2 * (int64_t)std::max(num_cus, 1);
+  return max_tokens <= kWholeTokens || items >= 4 * G ||
+         (max_tokens <= kWholeTable && items * 16 >= 3 * G && max_tokens * G <= kWholeShare * items);
 }
 static bool attn_whole(const AttnCall& c) {
   return attn_whole(c.batch, c.hkv, c.max_blocks * c.kv.bs, c.num_cus);

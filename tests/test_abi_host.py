@@ -291,6 +291,21 @@ def test_attention_gives_a_wave_an_item_only_while_no_item_is_long():
     assert (p["combine"], p["part_tokens"], p["wave_items"]) == (1, 512, 0)
 
 
+@pytest.mark.parametrize("hkv,batch,tokens,whole", [
+    (8, 1, 768, 1), (8, 1, 784, 0),                       # what one workgroup reads in a combine launch's time
+    (8, 11, 1024, 0), (8, 12, 1024, 1), (2, 48, 1024, 1),  # 96 items: 3 for 16 workgroups
+    (8, 12, 1248, 1), (8, 12, 1264, 0), (8, 16, 1664, 1), (8, 16, 1680, 0), (8, 20, 2048, 1), (8, 19, 2048, 0),
+    (8, 255, 2048, 1), (8, 255, 2064, 0),                 # past 2048 tokens only many items stay whole
+    (8, 256, 2064, 1), (8, 256, 1 << 20, 1),
+])
+def test_attention_stays_one_launch_while_tables_are_short(hkv, batch, tokens, whole):
+    p = _attention_plan([tokens] * batch, hkv)
+    assert p["combine"] == 1 - whole
+    assert (p["part_tokens"] == 1 << 20) == bool(whole)
+    if whole:
+        assert p["items"] == batch * hkv
+
+
 def test_attention_plan_skips_positions_outside_their_table_and_rejects_bad_arguments():
     import paper_2605_28095_amd as sidp
     assert sidp.sidp_attention_plan([-1, 31, 32, 2 ** 31 - 1], 2, 8)["items"] == 8

@@ -5,9 +5,10 @@ Compared with the oracle as the other attention cases are."""
 
 import numpy as np
 import pytest
+import torch
 
 import synth
-from gpu_helpers import assert_bf16_within_ulp
+from gpu_helpers import assert_bf16_within_ulp, kernels_of
 from test_gpu_kernels import _attn_oracle, _attn_run, _attn_setup
 
 pytestmark = pytest.mark.gpu
@@ -32,6 +33,7 @@ def _mixed(n, hi, seed):
     (64, 8, 128, _mixed(255, 64, 7) + [8192]),                 # whole sequences, one long among 255 short
     (16, 8, 64, [40] * 255 + [1024]),                          # the longest sequence that a lone wave takes there
     (16, 8, 64, [40] * 255 + [1025]),                          # and one token more
+    (16, 8, 64, _mixed(20, 2000, 8) + [2048]),                 # whole sequences on fewer items than workgroups
 ])
 def test_split_attention_parity(lib, hq, hkv, d, seqs):
     cfg = synth.get_config("tiny_layer", num_q_heads=hq, num_kv_heads=hkv, head_dim=d)
@@ -40,3 +42,27 @@ def test_split_attention_parity(lib, hq, hkv, d, seqs):
     want = _attn_oracle(cfg, ctx, tables, k, v, q)
     pv = _attn_oracle(cfg, ctx, tables, k, v, q, absv=True)
     assert_bf16_within_ulp(got, want, what=f"split attention {hq}/{hkv} x {d}", abs_tol=2.0 ** -12 * pv)
+
+
+@pytest.mark.parametrize("batch,tokens,split", [(24, 1500, 0), (12, 1024, 0), (11, 1024, 1), (20, 2049, 1)])
+def test_combine_is_launched_only_for_split_sequences(lib, batch, tokens, split):
+    cfg = synth.get_config("tiny_layer", num_q_heads=8, num_kv_heads=8, head_dim=64)
+    maxb = -(-tokens // 16)
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    assert lib.sidp_attention_plan([tokens - 1] * batch, maxb, 8, cus)["combine"] == split
+    nblk = batch * maxb
+    h = lib.sidp_create(lib.make_config(dict(cfg, num_layers=1), batch, maxb * 16))
+    try:
+        kc = torch.zeros(nblk, 8, 8, 16, 8, dtype=torch.bfloat16, device="cuda")
+        vc = torch.zeros(nblk, 8, 64, 16, dtype=torch.bfloat16, device="cuda")
+        lib.sidp_kv_attach(h, kc, vc, nblk, 1)
+        bt = torch.arange(nblk, dtype=torch.int32, device="cuda").view(batch, maxb)
+        pos = torch.full((batch,), tokens - 1, dtype=torch.int32, device="cuda")
+        q = torch.ones(batch, 8, 64, dtype=torch.bfloat16, device="cuda")
+        out = torch.empty_like(q)
+        ran = kernels_of(lambda: lib.sidp_attention(h, q, 0, pos, bt, maxb, batch, out))
+        assert sum("k_attn" in name for name in ran) == 2 + split, ran  # plan, attention, combine
+        assert any("k_attn_combine" in name for name in ran) == bool(split), ran
+        lib.sidp_sync(h)
+    finally:
+        lib.sidp_destroy(h)
