@@ -69,7 +69,9 @@ static bool attn_whole(const AttnCall& c) {
 // 4-8K (190, 512) 25.2 / 36.2, 8 of 0.5-2K (160, 384) 26.4 / 33.9, 5 of 4-8K
 // (480, 1024) 37.1 / 43.0, 16 of 1-8K (1150, 3072) 65.8 / 73.0; at 32 of 1-8K
 // (2300) 2048 is the best (119; 3072 122, 6144 130), at 64 (4600) 4096 204
-// against 216 for 2048 and 210 whole, at 128 (9200) 8192 393 against 421.
+// against 216 for 2048 and 210 whole, at 128 (9200) 8192 393 against 421. Neither
+// multiple is best on all of 1000-2000: there items decide that just fill the CUs
+// or not (12 of 8190, mean 1535: 3072 tokens 71.6, 4096 73.0, 1536 83.8).
 constexpr int kMinLen = 256;
 constexpr float kShare = 2.7f, kShareLong = 1.3f, kLongMean = 1500.f;
 constexpr int kMaxLen = 1 << 20;  // no sequence is longer
@@ -80,6 +82,20 @@ __host__ __device__ inline int split_len(float mean) {
   const int p = 1 << (31 - __builtin_clz((unsigned)x));
   return p + p / 2 <= x ? p + p / 2 : p;
 }
+
+// Whether a list of `items` takes the next longer length: it is up to a fifth
+// longer than one item a CU (G workgroups, two a CU). The few CUs that get two
+// items then take almost twice as long as the rest, while with the next length no
+// CU gets a second one. Length by the mean / next (tokens, items: us a call on the
+// 70B heads): 11 sequences of 4095 1536, 264: 52.2 / 2048, 176: 41.6; 3 of 16000
+// 1536, 264: 51.4 / 2048, 192: 42.7; 12 of 3000 1024, 288: 46.1 / 1536, 192: 35.9;
+// 16 of 1-8K 3072, 280: 72.8 / 4096, 224: 67.3; 3 of 1-8K 512, 272: 30.8 / 768, 184:
+// 25.9. From 1.2 to 1.5 items a CU the next length is as often the slower one, and
+// just past two items a CU no neighbour is the better rule (72 of 8190, 576 items
+// of 8192: 438, and 412 with 2048 tokens; the rule's largest loss, with 36 of 8190
+// 233 / 215 and 128 of 256-512 beside eight of 4000 88 / 80).
+__host__ __device__ inline bool split_crowded(int64_t items, int G) { return 2 * items > G && 10 * items <= 6 * (int64_t)G; }
+__host__ __device__ inline int next_len(int p) { return p >= kMaxLen ? p : p & (p - 1) ? p / 3 * 4 : p + p / 2; }
 
 // With more items than workgroups and at most this many tokens an item on
 // average, a wave takes an item by itself: four waves on one would each read a
@@ -158,6 +174,7 @@ __global__ void __launch_bounds__(256) k_attn_plan(const int32_t* __restrict__ p
   extern __shared__ __attribute__((aligned(16))) uint32_t s_key[];
   __shared__ int s_sum[4];
   __shared__ int s_longest[4];
+  __shared__ int s_items[4];
   __shared__ int s_scan[4];
   __shared__ int s_short[4];
   const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
@@ -182,7 +199,16 @@ __global__ void __launch_bounds__(256) k_attn_plan(const int32_t* __restrict__ p
   }
   __syncthreads();
   const float tokens = 16.f * (float)(s_sum[0] + s_sum[1] + s_sum[2] + s_sum[3]);
-  const int ptok = whole ? kMaxLen : split_len(tokens * (float)hkv / (float)G);
+  int ptok = kMaxLen;
+  if (!whole) {
+    ptok = split_len(tokens * (float)hkv / (float)G);
+    int items = 0;
+    for (int b = b0; b < b1; b++) items += (s_seq[b] + ptok - 1) / ptok;
+    items = wave_sum_i(items);
+    if (lane == 0) s_items[wave] = items;
+    __syncthreads();
+    if (split_crowded((int64_t)(s_items[0] + s_items[1] + s_items[2] + s_items[3]) * hkv, G)) ptok = next_len(ptok);
+  }
   // full partitions of each sequence, their exclusive prefix, and the keys of the short ones
   int local = 0, shorts = 0;
   for (int b = b0; b < b1; b++) {
@@ -676,8 +702,16 @@ AttnPlan plan_attention(const int32_t* positions, int batch, int max_tokens, int
   AttnPlan p;
   p.combine = !attn_whole(batch, hkv, max_tokens, num_cus);
   p.part_tokens = p.combine ? split_len(tokens * (float)hkv / (float)G) : kMaxLen;
-  int listed = 0;
-  for (int b = 0; b < batch; b++) listed += (tokens_of(b) + p.part_tokens - 1) / p.part_tokens;
+  auto count = [&] {
+    int n = 0;
+    for (int b = 0; b < batch; b++) n += (tokens_of(b) + p.part_tokens - 1) / p.part_tokens;
+    return n;
+  };
+  int listed = count();
+  if (p.combine && split_crowded((int64_t)listed * hkv, G)) {
+    p.part_tokens = next_len(p.part_tokens);
+    listed = count();
+  }
   p.items = listed * hkv;
   p.wave_items = attn_solo(p.items, tokens / (float)std::max(listed, 1), std::min(longest, p.part_tokens), G);
   return p;

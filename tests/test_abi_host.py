@@ -306,6 +306,17 @@ def test_attention_stays_one_launch_while_tables_are_short(hkv, batch, tokens, w
         assert p["items"] == batch * hkv
 
 
+@pytest.mark.parametrize("seqs,part,items", [
+    ([4095] * 10, 1536, 240), ([4095] * 11, 2048, 176),      # 264 items of 1536 would give 8 CUs two
+    ([3000] * 3, 384, 192), ([3000] * 2, 256, 192),
+    ([16000] * 3, 2048, 192), ([4096] * 28, 2048, 448),      # 448 items: past a fifth over the CUs
+    ([1 << 20], 16384, 512),                                 # the longest sequence
+])
+def test_attention_partitions_do_not_crowd_a_few_compute_units(seqs, part, items):
+    p = _attention_plan(seqs)
+    assert (p["combine"], p["part_tokens"], p["items"]) == (1, part, items)
+
+
 def test_attention_plan_skips_positions_outside_their_table_and_rejects_bad_arguments():
     import paper_2605_28095_amd as sidp
     assert sidp.sidp_attention_plan([-1, 31, 32, 2 ** 31 - 1], 2, 8)["items"] == 8

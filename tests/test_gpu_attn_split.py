@@ -33,6 +33,7 @@ def _mixed(n, hi, seed):
     (64, 8, 128, _mixed(255, 64, 7) + [8192]),                 # whole sequences, one long among 255 short
     (16, 8, 64, [40] * 255 + [1024]),                          # the longest sequence that a lone wave takes there
     (16, 8, 64, [40] * 255 + [1025]),                          # and one token more
+    (16, 8, 64, [3000, 2999, 3072]),                           # 384-token partitions, the next length over the mean's
     (16, 8, 64, _mixed(20, 2000, 8) + [2048]),                 # whole sequences on fewer items than workgroups
 ])
 def test_split_attention_parity(lib, hq, hkv, d, seqs):
