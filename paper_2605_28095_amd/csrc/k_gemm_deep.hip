@@ -97,15 +97,17 @@ __global__ void __launch_bounds__(64 * W, W > 4 ? 1 : 2) k_gemm_deep(GemmArgs a)
   const uint32_t w_lane = (uint32_t)lane * 16u;
 
   // Activation pieces this wave fetches: LDS chunk p (row p / 8, slot p % 8)
-  // holds the row's chunk (p % 8) ^ ((row / 2) & 7). Rows past M re-read the
-  // last row (their results are not stored).
+  // holds the row's chunk (p % 8) ^ ((row / 2) & 7). Rows past M lie past the
+  // buffer, so nothing is fetched for them (their results are not stored). Fetching
+  // the last row in their place filled the address units and the MFMAs with its
+  // values: over 83 shapes of cold weights 100 and 129-176 rows took 3% longer.
   uint32_t x_off[XJ];
   int x_blk[XJ];
 #pragma unroll
   for (int j = 0; j < XJ; j++) {
     x_blk[j] = min(wave + j * W, kXBlocks - 1);
     const int p = x_blk[j] * 64 + lane, r = p >> 3, c = (p & 7) ^ ((r >> 1) & 7);
-    x_off[j] = (uint32_t)(((size_t)min(row0 + r, a.M - 1) * a.K + c * 8) * 2);
+    x_off[j] = row0 + r < a.M ? (uint32_t)(((size_t)(row0 + r) * a.K + c * 8) * 2) : kOutOfRange;
   }
 
   f32x16_t acc[MF][2];

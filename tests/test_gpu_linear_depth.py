@@ -67,7 +67,7 @@ def test_wide_workgroups_and_large_weights(lib, m, n, k, epi):
     _check(lib, m, n, k, epi, _x(m, k))
 
 
-@pytest.mark.parametrize("m", [20, 50, 200])
+@pytest.mark.parametrize("m", [20, 50, 97, 129, 200])
 def test_rows_stay_apart_with_infinities_and_a_ragged_k(lib, m):
     """A row of infinities or NaN reaches its own outputs only, also where the
     pieces of a ragged k-tile run on into the next row."""
