@@ -27,9 +27,9 @@
 //    or by the kernel that consumes the result (the RoPE/KV-append kernel for
 //    QKV, the residual + RMSNorm reduction for O and down; LinearCall's
 //    defer_reduce and norm_out select this).
-//  * k_gemm runs beside slot fills (and on unaligned activations); projections
-//    with the chip to themselves run on k_gemm_deep (k_gemm_deep.hip), the same
-//    tiles and sums with a deeper pipeline.
+//  * k_gemm runs beside slot fills, on unaligned activations and where its short
+//    start pays (deep_pays); other projections with the chip to themselves run on
+//    k_gemm_deep (k_gemm_deep.hip), the same tiles and sums with a deeper pipeline.
 //  * k_gemm_lw is the same contraction with 256-row workgroups whose weight
 //    tiles are staged once per CU in LDS (direct-to-LDS loads) and shared by
 //    both 128-row halves. It halves the weight loads per flop but needs twice
@@ -669,6 +669,38 @@ GemmPlan plan_linear(int m, int n, int k, int epilogue, int num_cus) {
   return p;
 }
 
+// Whether k_gemm_deep is the faster form of kernel 0 alone on the chip. It is not
+// (us a call, weights from HBM, k_gemm / deep; two figures: two cards)
+//  * where a second row block of at most kThinRows rows shares weights too large to
+//    stay cached over a long k range: 8192 x 28672 at 129, 144, 160 rows 128 / 143,
+//    133 / 139, 134 / 131, 6144 x 28672 98 / 114, 103 / 110, 103 / 98; a shorter range
+//    14336 x 8192 at 144 73 / 64, gate/up 28672 x 8192 227 / 211;
+//  * where the row blocks of a full chip have few k-tiles each (the pipeline's start,
+//    three stages and two weight tiles, is then most of it): 200 rows of 4096 x 2048
+//    (4 k-tiles) 23.6 / 27.1, 23.1 / 25.0, of 4096 x 4096 (8) 25.3 / 28.3, 25.3 / 25.8;
+//    512 rows of 5120 x 1024 (5) 26.6 / 30.6, 26.5 / 26.5; 256 rows of 10240 x 1024
+//    (5) 25.8 / 28.7, 25.0 / 27.3. With 16 to 28 k-tiles and two row blocks the deep
+//    one is 4% slower on one card and 3% faster on the other; on nine tenths of a
+//    chip or less (12544 x 2048, 196 workgroups) it is 3-4% faster;
+//  * where some CUs get two 4-wave workgroups and no row block is ragged, or the k
+//    range is short: 384 rows of 24576 x 8192 213 / 235, of a 13824 x 5120 gate/up 142
+//    / 157, 512 of 18304 x 4096 114 / 120, 300 of 24576 x 1024 39.4 / 40.4; but 300 of
+//    24576 x 4096 111 / 107, of an 11008 x 4096 gate/up 96.9 / 85.1.
+constexpr size_t kThinBytes = (size_t)150 << 20;
+constexpr int kThinRows = 24;
+constexpr int kThinTiles = 224;       // k-tiles
+constexpr int kFewTiles = 32;         // k-tiles of a split times the row blocks
+constexpr int kFewTilesUnsplit = 32;  // k-tiles
+
+static bool deep_pays(const GemmArgs& a, const GemmPlan& p, int num_cus) {
+  const int mblocks = (a.M + p.rows - 1) / p.rows, tiles = (a.NG + p.waves - 1) / p.waves, KT = a.KP / kBK;
+  const int64_t grid = (int64_t)tiles * mblocks * p.splits;
+  if (mblocks == 1) return true;
+  if (a.M <= 128 + kThinRows && KT >= kThinTiles && (size_t)a.NG * 64 * a.KP * 2 >= kThinBytes) return false;
+  if (p.splits > 1) return grid * 10 < 9 * (int64_t)num_cus || (int64_t)KT * mblocks > kFewTiles * (int64_t)p.splits;
+  return p.waves > kWaves || grid <= num_cus || (a.M % p.rows != 0 && KT > kFewTilesUnsplit);
+}
+
 hipError_t launch_linear(const LinearCall& c, hipStream_t s) {
   GemmArgs a;
   a.x = (const uint16_t*)c.x;
@@ -693,15 +725,9 @@ hipError_t launch_linear(const LinearCall& c, hipStream_t s) {
   // 8 a wide unsplit k_gemm, 0 the 4-wave k_gemm
   const GemmPlan plan = plan_linear(c.m, c.n, c.k, c.epilogue, c.num_cus);
   const int wide = plan.kernel == 1 ? -1 : plan.waves > kWaves ? plan.waves : 0;
-  // Alone on the chip the deep pipeline is the faster form of kernel 0 except
-  // where a second row block of at most 32 rows shares weights too large to stay
-  // cached (kernel alone, us, k_gemm / deep: 470 MB at 129, 145, 160, 192 rows 219 /
-  // 236, 208 / 228, 220 / 227, 225 / 223; 484 MB 130 / 149, 130 / 143, 128 / 136,
-  // 127 / 112; 168 MB 49 / 52, 49 / 49, 49 / 45). Beside a slot fill the shallow
-  // one is faster (both sides' times in k_gemm_deep.hip). The deep one's
-  // direct-to-LDS loads need 16-byte aligned activations.
-  const bool thin_block = c.m > 128 && c.m <= 160 && (size_t)a.NG * 64 * a.KP * 2 >= kNtBytes;
-  const bool deep = plan.kernel == 0 && !c.beside_fill && !thin_block && (uintptr_t)c.x % 16 == 0;
+  // Beside a slot fill the shallow kernel is the faster one (both sides' times in
+  // k_gemm_deep.hip); the deep one's direct-to-LDS loads need 16-byte aligned activations.
+  const bool deep = plan.kernel == 0 && !c.beside_fill && (uintptr_t)c.x % 16 == 0 && deep_pays(a, plan, c.num_cus);
   hipError_t e;
   if (a.splits == 1) {
     if (deep) e = launch_gemm_deep(a, c.epilogue, plan.rows, plan.waves, s);

@@ -5,8 +5,12 @@ column groups. Compared with float64 on every element: a sum of k products of
 bf16 numbers accumulated in fp32 is within 2^-20 of sum |x w| of the exact one,
 plus half a bf16 spacing (2^-9 of the value) where the output is bf16."""
 
+import re
+
 import pytest
 import torch
+
+from gpu_helpers import kernels_of
 
 pytestmark = pytest.mark.gpu
 
@@ -99,3 +103,36 @@ def test_split_reduction_of_odd_widths(lib, n, epi):
     """Split-K outputs whose width is no multiple of four columns are reduced one column a thread."""
     assert lib.sidp_linear_plan(17, n, 4104, epi)["splits"] > 1
     _check(lib, 17, n, 4104, epi, _x(17, 4104))
+
+
+def _kernel(lib, m, n, k, epi):
+    """The projection kernel that a call launches."""
+    cols = 2 * (-(-n // 32) * 32) if epi == 2 else n
+    packed = torch.zeros(lib.sidp_packed_bytes(cols, k), dtype=torch.uint8, device="cuda")
+    x = torch.zeros(m, k, dtype=torch.bfloat16, device="cuda")
+    out = torch.empty(m, n, dtype=torch.float32 if epi == 1 else torch.bfloat16, device="cuda")
+    resid = torch.zeros(m, n, device="cuda") if epi == 1 else None
+    ran = kernels_of(lambda: lib.sidp_linear_noalloc(x, m, k, packed, n, epi, None, resid, out))
+    return re.search(r"k_gemm\w*", next(name for name in ran if "k_gemm" in name)).group(0)
+
+
+@pytest.mark.parametrize("m,n,k,epi,kernel", [
+    # a thin second row block: 24 rows, 14336 k and 150 MiB
+    (152, 8192, 14336, 1, "k_gemm"), (153, 8192, 14336, 1, "k_gemm_deep"), (152, 8192, 14272, 1, "k_gemm_deep"),
+    (152, 5120, 14336, 1, "k_gemm_deep"), (128, 8192, 14336, 1, "k_gemm_deep"),
+    # few k-tiles on a full chip: 16 a split with two row blocks, 8 with four
+    (200, 4096, 8192, 0, "k_gemm"), (200, 4096, 8256, 0, "k_gemm_deep"), (128, 4096, 4096, 0, "k_gemm_deep"),
+    (512, 2048, 4096, 0, "k_gemm"), (512, 2048, 4160, 0, "k_gemm_deep"), (200, 12544, 1024, 0, "k_gemm_deep"),
+    # two 4-wave workgroups on some CUs: 288 of them, whole row blocks or 32 k-tiles
+    (384, 24576, 2112, 0, "k_gemm"), (383, 24576, 2112, 0, "k_gemm_deep"), (383, 24576, 2048, 0, "k_gemm"),
+    (384, 18304, 2112, 0, "k_gemm_deep"), (512, 28672, 1024, 2, "k_gemm_deep"),
+])
+def test_the_deep_pipeline_runs_where_it_is_the_faster_one(lib, m, n, k, epi, kernel):
+    assert _kernel(lib, m, n, k, epi) == kernel
+
+
+@pytest.mark.parametrize("m,n,k,epi", [(152, 8192, 14336, 1), (200, 4096, 2056, 0), (512, 2048, 1032, 1),
+                                       (384, 24576, 328, 0), (300, 24576, 1032, 0), (257, 11008, 264, 2)])
+def test_row_blocks_on_the_shallow_kernel(lib, m, n, k, epi):
+    assert _kernel(lib, m, n, k, epi) == "k_gemm"
+    _check(lib, m, n, k, epi, _x(m, k))
