@@ -481,9 +481,12 @@ __global__ void __launch_bounds__(256) k_splitk_reduce(GemmArgs a) {
   }
 }
 
-// Four columns a thread only where that leaves a workgroup per CU: 29 rows of
-// 3032 SwiGLU columns (10 splits) take 20.5 us a call with four, 20.1 with one.
-constexpr int64_t kVecOutputs = 256 * 1024;
+// Four columns a thread only where that leaves more than a workgroup and a half a
+// CU. Over 83 shapes, a call's time with four columns over its time with one: at
+// 262144 outputs 1.02 (128 rows of 2048 columns, 16 splits 21.6 / 20.2 us, 64 of 4096
+// 20.4 / 19.2; but 257 of 1024 20.1 / 26.7), up to 400000 1.00, up to 524288 0.98,
+// from 2 million on 0.95.
+constexpr int64_t kVecOutputs = 400 * 1024;
 
 template <int EPI>
 static hipError_t launch_splitk_reduce(const GemmArgs& a, hipStream_t s) {

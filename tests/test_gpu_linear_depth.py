@@ -136,3 +136,14 @@ def test_the_deep_pipeline_runs_where_it_is_the_faster_one(lib, m, n, k, epi, ke
 def test_row_blocks_on_the_shallow_kernel(lib, m, n, k, epi):
     assert _kernel(lib, m, n, k, epi) == "k_gemm"
     _check(lib, m, n, k, epi, _x(m, k))
+
+
+@pytest.mark.parametrize("m,n,k,columns", [(100, 4096, 2056, 4), (99, 4096, 2056, 1), (128, 2048, 1032, 1), (200, 2049, 1032, 1)])
+def test_split_reduction_reads_four_columns_a_thread_of_large_outputs(lib, m, n, k, columns):
+    """From 409600 outputs on, in rows of a multiple of four columns."""
+    packed = torch.zeros(lib.sidp_packed_bytes(n, k), dtype=torch.uint8, device="cuda")
+    x = torch.zeros(m, k, dtype=torch.bfloat16, device="cuda")
+    out = torch.empty(m, n, dtype=torch.bfloat16, device="cuda")
+    ran = kernels_of(lambda: lib.sidp_linear_noalloc(x, m, k, packed, n, 0, None, None, out))
+    assert any(f"k_splitk_reduce<0, {columns}>" in name for name in ran), ran
+    _check(lib, m, n, k, 0, _x(m, k))
