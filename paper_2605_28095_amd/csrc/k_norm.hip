@@ -6,16 +6,19 @@
 
 namespace sidp {
 
+// A chunk's squares, with the roundings fixed: both kernels below sum a row in the
+// same order, so a row's bits do not depend on which of them takes it.
+__device__ __forceinline__ float sum_sq4(const float4& v) {
+  return fmaf(v.w, v.w, fmaf(v.z, v.z, fmaf(v.x, v.x, v.y * v.y)));
+}
+
 __global__ void __launch_bounds__(256) k_rmsnorm(const float* __restrict__ x, const uint16_t* __restrict__ g,
                                                  float eps, uint16_t* __restrict__ out, int n) {
   __shared__ float red[4];
   const int row = blockIdx.x;
   const float* xr = x + (int64_t)row * n;
   float ss = 0.f;
-  for (int i = threadIdx.x * 4; i < n; i += 1024) {
-    const float4 v = *(const float4*)(xr + i);
-    ss += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
-  }
+  for (int i = threadIdx.x * 4; i < n; i += 1024) ss += sum_sq4(*(const float4*)(xr + i));
   ss = wave_sum(ss);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
   __syncthreads();
@@ -36,14 +39,16 @@ __global__ void __launch_bounds__(256) k_rmsnorm(const float* __restrict__ x, co
 
 // The same for rows of up to kRrnMaxChunks * kRrnThreads * 4 columns: the row
 // stays in registers between the two passes and every load is in flight at
-// once. A launch of a few rows is one latency chain: the first norm of a step on
-// 16 rows of 8192 columns takes 5.1 us, with the looped kernel 7.6.
+// once. A launch of a few rows is one latency chain: 16 rows of 8192
+// columns back to back 4.3 -> 4.0 us, 256 rows 4.8 -> 4.1, of 16384 11.1 -> 5.8. The first
+// 256 threads sum the chunks' squares in the looped kernel's order, out of LDS.
 constexpr int kRrnThreads = 1024;
 constexpr int kRrnMaxChunks = 4;  // rows of up to 16384 columns
 
 __global__ void __launch_bounds__(kRrnThreads) k_rmsnorm_row(const float* __restrict__ x, const uint16_t* __restrict__ g,
                                                             float eps, uint16_t* __restrict__ out, int n) {
-  __shared__ float red[kRrnThreads / 64];
+  __shared__ float sq[kRrnMaxChunks * kRrnThreads];
+  __shared__ float red[4];
   const float* xr = x + (int64_t)blockIdx.x * n;
   float4 v[kRrnMaxChunks];
   uint2 gg[kRrnMaxChunks];
@@ -56,15 +61,19 @@ __global__ void __launch_bounds__(kRrnThreads) k_rmsnorm_row(const float* __rest
       gg[c] = *(const uint2*)(g + i);
     }
   }
-  float ss = 0.f;
 #pragma unroll
-  for (int c = 0; c < kRrnMaxChunks; c++) ss += v[c].x * v[c].x + v[c].y * v[c].y + v[c].z * v[c].z + v[c].w * v[c].w;
-  ss = wave_sum(ss);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
+  for (int c = 0; c < kRrnMaxChunks; c++) sq[c * kRrnThreads + threadIdx.x] = sum_sq4(v[c]);
   __syncthreads();
-  float total = 0.f;
+  if (threadIdx.x < 256) {  // whole waves
+    float ss = 0.f;
 #pragma unroll
-  for (int w = 0; w < kRrnThreads / 64; w++) total += red[w];
+    for (int k = 0; k < kRrnMaxChunks * 4; k++)
+      if (k * 1024 < n) ss += sq[k * 256 + threadIdx.x];
+    ss = wave_sum(ss);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
+  }
+  __syncthreads();
+  const float total = red[0] + red[1] + red[2] + red[3];
   const float r = 1.0f / sqrtf(total / (float)n + eps);
   uint16_t* orow = out + (int64_t)blockIdx.x * n;
 #pragma unroll
@@ -81,8 +90,8 @@ __global__ void __launch_bounds__(kRrnThreads) k_rmsnorm_row(const float* __rest
 
 hipError_t launch_rmsnorm(const float* x, const void* gain, float eps, void* out, int rows, int n, hipStream_t s) {
   if (rows <= 0) return hipSuccess;
-  // Where every thread of the wide workgroup has columns (8192: 256 rows 6.1 ->
-  // 4.2 us, 2048 rows 26.6 -> 20.5; 4096 rows of 1024 columns 6.5 -> 14.0).
+  // Where every thread of the wide workgroup has columns (4096 rows of 1024 columns
+  // would take 14.0 us instead of 6.5).
   if (n >= kRrnThreads * 4 && n <= kRrnMaxChunks * kRrnThreads * 4)
     k_rmsnorm_row<<<rows, kRrnThreads, 0, s>>>(x, (const uint16_t*)gain, eps, (uint16_t*)out, n);
   else

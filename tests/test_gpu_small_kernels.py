@@ -25,6 +25,43 @@ def test_rmsnorm_row_lengths(lib, rows, n):
     assert_bf16_within_ulp(bits(out), want, what="rmsnorm")
 
 
+def _fma(a, b, c):
+    """float32 a * b + c rounded once (but for a double rounding one time in 2^29)."""
+    return (a.astype(np.float64) * b.astype(np.float64) + c.astype(np.float64)).astype(np.float32)
+
+
+def _butterfly_sum(v):
+    for o in (32, 16, 8, 4, 2, 1):
+        v = v + v[..., np.arange(64) ^ o]
+    return v[..., 0]
+
+
+@pytest.mark.parametrize("rows,n", [(64, 1024), (256, 8192), (64, 5120), (16, 16384), (16, 16388), (64, 4100)])
+def test_rmsnorm_sums_every_row_length_in_one_order(lib, rows, n):
+    """Both kernels sum thread t's chunks 1024 columns apart, then the wave's
+    threads pairwise, then the four waves: the same float32 roundings, hence the
+    same bits as written out here, whichever kernel takes the row."""
+    g = torch.Generator().manual_seed(rows + n)
+    x = torch.randn(rows, n, generator=g) * 3.0
+    gain = (1 + 0.1 * torch.randn(n, generator=g)).to(torch.bfloat16)
+    out = torch.empty(rows, n, dtype=torch.bfloat16, device="cuda")
+    lib.sidp_rmsnorm(x.cuda(), gain.cuda(), 1e-5, out, rows, n)
+    torch.cuda.synchronize()
+    v = x.numpy()
+    padded = np.zeros((rows, -(-n // 1024) * 1024), np.float32)
+    padded[:, :n] = v
+    q = padded.reshape(rows, -1, 256, 4)  # [row, turn, thread, column of the chunk]
+    q = _fma(q[..., 3], q[..., 3], _fma(q[..., 2], q[..., 2], _fma(q[..., 0], q[..., 0], q[..., 1] * q[..., 1])))
+    ss = np.zeros((rows, 256), np.float32)
+    for k in range(q.shape[1]):
+        ss = ss + q[:, k]
+    w = _butterfly_sum(ss.reshape(rows, 4, 64))
+    total = ((w[:, 0] + w[:, 1]) + w[:, 2]) + w[:, 3]
+    r = (np.float32(1) / np.sqrt(total / np.float32(n) + np.float32(1e-5))).astype(np.float32)
+    want = (v * r[:, None]) * gain.float().numpy()
+    assert torch.equal(out.cpu(), torch.from_numpy(want).to(torch.bfloat16))
+
+
 @pytest.mark.parametrize("name", ["tiny_layer", "qwen3_32b_layer"])
 def test_rope_append_unaligned_inputs_bitexact(lib, name):
     cfg = synth.get_config(name, qk_norm=1, num_layers=1)
