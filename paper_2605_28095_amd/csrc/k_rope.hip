@@ -5,8 +5,8 @@
 // sequence and a workgroup 16 (32); the other half of a rotate-half pair sits
 // D / 16 lanes away. Bound by latency, not bytes: 16-byte loads and stores and
 // several heads to a wave keep a launch at one round of waves on the chip (256
-// sequences of 80 heads with QK-norm 8.1 us; a wave per head, 2 bytes a lane and
-// load, 10.4). The projection output is read either as bf16 or, when the QKV
+// sequences of 80 heads with QK-norm 7.9 us; a wave per head, 2 bytes a lane and
+// load, 9.6). The projection output is read either as bf16 or, when the QKV
 // projection left split-K partials, reduced here: the partials are summed in
 // split order, the bias added and the result rounded to bf16, which is the
 // same value the projection's own reduction would have stored.
@@ -29,6 +29,31 @@ __device__ __forceinline__ void load8(const uint16_t* p, float (&v)[8]) {
 #pragma unroll
     for (int i = 0; i < 8; i++) v[i] = bf2f(p[i]);
   }
+}
+
+// The sum of a head's squares, on each of its D / 8 lanes: rotate-half pairs (i, i +
+// D/2) first, then pairs of i that differ in their highest bit, and so on down, so
+// that the roundings are those of one pair per lane and a butterfly over the lanes.
+// Each of the first steps hands half of a lane's sums over and keeps the other half.
+template <int D>
+__device__ __forceinline__ float head_sum_sq(const float (&x)[8], int sub) {
+  constexpr int kLanes = D / 8;
+  const bool h4 = sub & (kLanes / 2), h2 = sub & (kLanes / 4), h1 = sub & (kLanes / 8);
+  float t[4], u[2];
+#pragma unroll
+  for (int j = 0; j < 4; j++) {  // dims j of the lane's eight in its first half, 4 + j in its second
+    const float own = h4 ? x[4 + j] : x[j];
+    const float other = __shfl_xor(h4 ? x[j] : x[4 + j], kLanes / 2, 64);
+    const float lo = h4 ? other : own, hi = h4 ? own : other;
+    t[j] = fmaf(hi, hi, lo * lo);
+  }
+#pragma unroll
+  for (int j = 0; j < 2; j++) u[j] = (h2 ? t[2 + j] : t[j]) + __shfl_xor(h2 ? t[j] : t[2 + j], kLanes / 4, 64);
+  float v = (h1 ? u[1] : u[0]) + __shfl_xor(h1 ? u[0] : u[1], kLanes / 8, 64);
+  if (D == 128) v += __shfl_xor(v, 1, 64);
+#pragma unroll
+  for (int o = kLanes / 2; o >= kLanes / 8; o >>= 1) v += __shfl_xor(v, o, 64);
+  return v;
 }
 
 template <int D, bool ALIGNED>
@@ -102,13 +127,9 @@ __global__ void __launch_bounds__(256) k_rope_append(RopeCall c) {
   }
   const uint16_t* gn = is_q ? c.g_q : c.g_k;
   if (gn) {
-    float g[8], ss = 0.f;
+    float g[8];
     load8<ALIGNED>(gn + d0, g);
-#pragma unroll
-    for (int i = 0; i < 8; i++) ss += x[i] * x[i];
-#pragma unroll
-    for (int o = kLanes / 2; o >= 1; o >>= 1) ss += __shfl_xor(ss, o, 64);
-    const float r = 1.0f / sqrtf(ss / (float)D + c.qk_eps);
+    const float r = 1.0f / sqrtf(head_sum_sq<D>(x, sub) / (float)D + c.qk_eps);
 #pragma unroll
     for (int i = 0; i < 8; i++) x[i] = x[i] * r * g[i];
   }

@@ -90,3 +90,35 @@ def test_rope_append_unaligned_inputs_bitexact(lib, name):
         outs.append((q.clone(), kc, vc))
     assert bool((outs[0][0] != 0).any())
     assert all(torch.equal(a, b) for a, b in zip(*outs))
+
+
+@pytest.mark.parametrize("name,batch", [("tiny_layer", 64), ("qwen3_32b_layer", 32)])
+def test_qk_norm_sums_a_head_in_one_order(lib, name, batch):
+    """A head's squares are summed as pairs (i, i + D/2) and then pairwise from
+    the highest bit of i down: the float32 roundings written out here, so the
+    queries at position 0 (no rotation) come out bit for bit."""
+    cfg = synth.get_config(name, qk_norm=1, num_layers=1)
+    Hq, Hkv, D = cfg["num_q_heads"], cfg["num_kv_heads"], cfg["head_dim"]
+    g = torch.Generator().manual_seed(9)
+    qkv = torch.randn(batch, Hq + 2 * Hkv, D, generator=g).to(torch.bfloat16)
+    gain = (1 + 0.1 * torch.randn(D, generator=g)).to(torch.bfloat16)
+    q = torch.empty(batch, Hq, D, dtype=torch.bfloat16, device="cuda")
+    kc = torch.zeros(batch, Hkv, D // 8, 16, 8, dtype=torch.bfloat16, device="cuda")
+    vc = torch.zeros(batch, Hkv, D, 16, dtype=torch.bfloat16, device="cuda")
+    pos = torch.zeros(batch, dtype=torch.int32, device="cuda")
+    bt = torch.arange(batch, dtype=torch.int32, device="cuda").view(batch, 1)
+    h = lib.sidp_create(lib.make_config(cfg, batch, 2048))
+    try:
+        lib.sidp_kv_attach(h, kc, vc, batch, 1)
+        lib.sidp_rope_append(h, qkv.cuda(), pos, bt, 1, batch, gain.cuda(), gain.cuda(), 0, q)
+        lib.sidp_sync(h)
+    finally:
+        lib.sidp_destroy(h)
+    x = qkv.float().numpy()
+    t = np.zeros((batch, Hq + 2 * Hkv, 64), np.float32)
+    t[..., :D // 2] = _fma(x[..., D // 2:], x[..., D // 2:], x[..., :D // 2] * x[..., :D // 2])
+    r = np.float32(1) / np.sqrt(_butterfly_sum(t) / np.float32(D) + np.float32(cfg["qk_norm_eps"]))
+    want = torch.from_numpy((x * r[..., None].astype(np.float32)) * gain.float().numpy()).to(torch.bfloat16)
+    assert torch.equal(q.cpu(), want[:, :Hq])
+    k = lib.k_blocks_from_lib(kc)[:, :, 0].cpu()
+    assert torch.equal(k, want[:, Hq:Hq + Hkv])
