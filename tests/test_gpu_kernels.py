@@ -241,13 +241,21 @@ def _attn_oracle(cfg, ctx, tables, k, v, q, absv=False):
                      for b in range(len(ctx))])
 
 
+# Around blocks, chunks and the partitions these lengths get on 256 CUs: 256 tokens with one or two KV heads, 1024 with
+# eight. They end inside, at and one token past a partition.
 ATTN_SEQS = [1, 2, 15, 16, 17, 31, 32, 33, 100, 511, 512, 513, 1024, 1500, 2047, 2048, 2049, 4096, 4097]
+
+
+def _assert_cut(lib, ctx, maxb, hkv, part_tokens):
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    assert lib.sidp_attention_plan(ctx, maxb, hkv, cus)["part_tokens"] == part_tokens
 
 
 @pytest.mark.parametrize("name,q_scale", [("tiny_layer", 1.0), ("llama70b_layer", 1.0), ("llama70b_layer", 4.0)])
 def test_attention_parity(lib, name, q_scale):
     cfg = synth.get_config(name)
     ctx, tables, nblk, k, v, q, maxb = _attn_setup(lib, cfg, ATTN_SEQS, q_scale=q_scale)
+    _assert_cut(lib, ctx, maxb, cfg["num_kv_heads"], {2: 256, 8: 1024}[cfg["num_kv_heads"]])
     got = _attn_run(lib, cfg, ctx, tables, nblk, k, v, q, maxb, regions=2, region=1)
     want = _attn_oracle(cfg, ctx, tables, k, v, q)
     pv = _attn_oracle(cfg, ctx, tables, k, v, q, absv=True)  # sum_j P_j |v_j|
@@ -265,8 +273,10 @@ def _many_short_seqs(n=2048, seed=11):
 ])
 def test_attention_parity_group_shapes(lib, hq, hkv, d, seqs):
     cfg = synth.get_config("tiny_layer", num_q_heads=hq, num_kv_heads=hkv, head_dim=d)
-    seqs = _many_short_seqs() if seqs == "many" else seqs
+    many = seqs == "many"
+    seqs = _many_short_seqs() if many else seqs
     ctx, tables, nblk, k, v, q, maxb = _attn_setup(lib, cfg, seqs)
+    _assert_cut(lib, ctx, maxb, hkv, 1 << 20 if many else 256)
     got = _attn_run(lib, cfg, ctx, tables, nblk, k, v, q, maxb)
     want = _attn_oracle(cfg, ctx, tables, k, v, q)
     pv = _attn_oracle(cfg, ctx, tables, k, v, q, absv=True)
@@ -274,13 +284,14 @@ def test_attention_parity_group_shapes(lib, hq, hkv, d, seqs):
 
 
 def test_attention_longest_context(lib):
-    """A sequence at the longest context a handle accepts (2^20 positions:
-    512 partitions merged by the combine kernel), ragged in its last block,
-    beside a short and a two-partition one."""
+    """A sequence at the longest context a handle accepts (2^20 positions: 256
+    partitions of 4096 tokens merged by the combine kernel), ragged in its last
+    block, beside a short one and ones of one, two and three partitions."""
     cfg = synth.get_config("tiny_layer")
-    seqs = [(1 << 20) - 21, 5, 2049]
+    seqs = [(1 << 20) - 21, 5, 2049, 4096, 4097, 8193]
     ctx, tables, nblk, k, v, q, maxb = _attn_setup(lib, cfg, seqs, nblk_extra=3)
     assert maxb * 16 + 16 == 1 << 20  # the handle's max_seq_len at its limit
+    _assert_cut(lib, ctx, maxb, cfg["num_kv_heads"], 4096)
     got = _attn_run(lib, cfg, ctx, tables, nblk, k, v, q, maxb)
     want = _attn_oracle(cfg, ctx, tables, k, v, q)
     pv = _attn_oracle(cfg, ctx, tables, k, v, q, absv=True)
