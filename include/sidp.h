@@ -386,9 +386,12 @@ int sidp_rmsnorm(const float *x, const void *gain, float eps, void *out, int32_t
 /* The launch sidp_linear, sidp_linear_noalloc and the decode step make for
  * the projection out[m, n] = x[m, k] W[n, k]^T with `epilogue` on a GPU with
  * `num_cus` compute units (host only, no device call). kernel: 0 = weights
- * streamed into registers by each 128-row block, 1 = 256-row workgroups whose
- * weight tiles are staged once in LDS (taken where kernel 0 would run one
- * unsplit round on under three quarters of the CUs). waves: per workgroup (4,
+ * streamed into registers by each 128-row block (two forms with the same tiles,
+ * sums and bits: a deep pipeline for projections alone on the chip, a shallow
+ * one beside a slot fill, for activations that are not 16-byte aligned and where
+ * it is the faster one), 1 = 256-row workgroups whose weight tiles are staged
+ * once in LDS (taken where kernel 0 would run one unsplit round on under three
+ * quarters of the CUs). waves: per workgroup (4,
  * 7 or 8). rows_per_workgroup: 32, 64, 128 or 256. splits: the split-K count
  * (fp32 partials reduced in split order). workgroups: the grid launched.
  * ws_bytes: bytes of partials (0 without a split). All outputs host,

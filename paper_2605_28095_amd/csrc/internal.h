@@ -36,9 +36,10 @@ bool gemm_fits(int m, int n_cols_packed, int k);  // within the kernels' 32-bit 
 int gemm_splits(int M, int n_cols_packed, int K, int num_cus);
 size_t gemm_ws_bytes(int M, int n_cols_packed, int K, int num_cus);
 // The launch launch_linear makes for an [m, k] x [n, k]^T projection: kernel
-// 0 = k_gemm (weights into registers), 1 = k_gemm_lw (256-row workgroups,
-// weight tiles staged in LDS); waves and rows per workgroup; split-K count;
-// workgroups launched; bytes of fp32 partials (0 without a split).
+// 0 = weights into registers (k_gemm_deep, or k_gemm beside a slot fill, on
+// unaligned activations and where it is the faster one), 1 = k_gemm_lw (256-row
+// workgroups, weight tiles staged in LDS); waves and rows per workgroup;
+// split-K count; workgroups launched; bytes of fp32 partials (0 without a split).
 struct GemmPlan {
   int kernel, waves, rows, splits, workgroups;
   size_t ws_bytes;

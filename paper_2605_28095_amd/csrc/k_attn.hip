@@ -2,8 +2,9 @@
 //
 // Work is a list of items (sequence b, partition p, KV head g). A planning
 // kernel, run once per set of positions, chooses the partition length: whole
-// sequences when the batch alone gives every workgroup several items, else a
-// length that follows the tokens these positions leave to each workgroup.
+// sequences when the batch alone gives every workgroup several items or the block
+// tables are short, else a length that follows the tokens these positions leave to
+// each workgroup and the number of items that makes.
 // It lists the full partitions first and then each sequence's shorter last
 // partition by decreasing length; a persistent grid of 4-wave workgroups
 // walks that list in snake order (workgroup w takes items w, 2G - 1 - w,
@@ -63,8 +64,8 @@ static bool attn_whole(const AttnCall& c) {
 // mean. A workgroup alone reads five times as fast as its share of HBM when all
 // read, so uneven items level out by themselves and few long items cost less
 // than the starts, merges and records of many short ones, until one item takes
-// as long as the whole launch should. Measured on the 70B heads (us a call, at
-// the length taken / at 2048 tokens, the multiple taken before): 1 sequence of
+// as long as the whole launch should. Measured on the 70B heads (us a call, at the
+// length that the mean gives / at 2048 tokens): 1 sequence of
 // 2000 (mean 31, 256 taken) 18.9 / 29.3, 1 of 8000 (125, 256) 24.8 / 35.5, 2 of
 // 4-8K (190, 512) 25.2 / 36.2, 8 of 0.5-2K (160, 384) 26.4 / 33.9, 5 of 4-8K
 // (480, 1024) 37.1 / 43.0, 16 of 1-8K (1150, 3072) 65.8 / 73.0; at 32 of 1-8K

@@ -515,14 +515,16 @@ bool gemm_fits(int m, int n_cols_packed, int k) {
 
 static int splits_for(int tiles, int mblocks, int KT, int num_cus);
 
-// Whether a projection runs on k_gemm_lw (256-row workgroups, weights staged
-// in LDS) rather than k_gemm (128-row blocks, weights into registers). Alone
-// at B = 256 the LDS-staged kernel is slower on all four 70B projections
-// (QKV 53 against 51 us, O 46 against 40, down 143-148 against 129-136,
-// gate/up 318-335 against 284-309, its reductions 5 us slower with twice the
-// splits); it wins where k_gemm would run a single unsplit round on under
-// three quarters of the CUs, as QKV at 512 rows does (160 workgroups: 128-132
-// us against 95-97 plus a 16 us reduction on 240).
+// Whether a projection runs on k_gemm_lw (256-row workgroups, weights staged in
+// LDS) rather than kernel 0 (128-row blocks, weights into registers): where kernel
+// 0 would run a single unsplit round on under three quarters of the CUs, as QKV
+// does from 385 rows on (160 workgroups). Alone on the chip against k_gemm_deep
+// (us a call, k_gemm_lw / k_gemm_deep, its reduction included): 10240 x 8192 at
+// 400, 448, 512 rows 99.8 / 97.6, 101.5 / 104.4, 108.2 / 113.4; 10240 x 5120 70.0 /
+// 66.3, 73.2 / 72.6, 79.5 / 77.5. Against k_gemm, which a streamed step would have
+// in its place, QKV at 512 rows takes 95-97 plus a 16 us reduction against 128-132. At
+// 256 rows it is slower than k_gemm on all four 70B projections (QKV 53 against 51
+// us, O 46 against 40, down 143-148 against 129-136, gate/up 318-335 against 284-309).
 static bool use_lds_weights(int M, int NG, int K, int num_cus) {
   if (M <= 128 || K % 64) return false;
   const int tiles = (NG + kWaves - 1) / kWaves, mblocks = (M + 127) / 128;
@@ -546,7 +548,11 @@ static int splits_for(int tiles, int mblocks, int KT, int num_cus) {
   // beside 134 MB of weights) costs more than the second workgroup's latency
   // hiding gains. Rounding down rather than to nearest keeps a few CUs from
   // running a second workgroup after the rest have finished (O and down at
-  // M=384: 192 workgroups instead of 288, the step 2% faster).
+  // M=384: 192 workgroups instead of 288, the step 2% faster). On k_gemm_deep two
+  // workgroups a CU are slower too (us a call, one / two: QKV 10240 x 8192 at 64,
+  // 256 rows 40.2 / 45.8, 57.6 / 72.8, O 37.8 / 43.0, 50.8 / 66.0, down 83.1 / 93.9,
+  // 129 / 146) but where the rounding leaves CUs idle (down at 300, 400 rows 193 /
+  // 177, 214 / 203).
   int s = num_cus / base;
   if (s < 1) s = 1;
   if (s > 16) s = 16;
@@ -636,7 +642,10 @@ static hipError_t launch_epi(const GemmArgs& a, hipStream_t s, int wide = 0) {
 // (rounds of 7 or 8), and a wide width is a candidate only while it gives at
 // least 0.8 workgroups per CU (fewer would leave CUs idle that the model
 // counts as busy); ties go to the wider one. A 70B-shaped gate/up (896 column
-// groups) gets 7 waves at 256 rows, exactly 256 workgroups; a 924-group one 8.
+// groups) gets 7 waves at 256 rows, exactly 256 workgroups; a 924-group one 8. On
+// k_gemm_deep (us a call, chosen width / 4 waves) gate/up 28672 x 8192 takes at 200,
+// 256, 384, 512 rows 219 / 237, 216 / 251, 358 / 374, 381 / 474; at 300, where 4 waves
+// leave the last rows' workgroups short, 345 / 318.
 // Returns 4, 7 or 8.
 static int unsplit_width(int m, int NG, int num_cus) {
   int wide = 4;

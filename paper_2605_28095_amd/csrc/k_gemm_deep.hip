@@ -2,8 +2,10 @@
 // splits and order of every sum, so the same bits) with a deeper pipeline, for
 // projections that have the chip to themselves.
 //
-// What bounds it: at up to 128 rows the weight stream, at 256 rows and more the
-// matrix pipe at the clock that the card's power allows (about 1.7 GHz here).
+// What bounds it: at up to 128 rows the weight stream; in wide launches of many rows
+// the matrix pipe at the clock that the card's power allows (512 rows of gate/up:
+// MFMA busy 72% of the time at 1.67 GHz); split launches of 256 rows neither (QKV: 31%
+// busy at 2.36 GHz, 202 MB in 50 us), with one wave a SIMD on 240 CUs over 43 k-tiles.
 // What k_gemm leaves idle is its k loop: activations pass through registers
 // into a double-buffered stage, so every 64-wide k-tile ends with their arrival,
 // LDS writes, a barrier and the first fragment reads, with nothing to multiply
@@ -32,11 +34,15 @@
 namespace sidp {
 
 // Non-temporal weight loads pay from kNtBytes of packed weights on and while at
-// most kNtRowBlocks row blocks read each weight (alone, us, cached / non-temporal):
-// 168 MB at 16, 64, 256 rows 33.8 / 32.4, 39.1 / 40.4, 64.4 / 62.5; 262 MB at 16,
-// 64, 128, 256 rows 50.7 / 46.4, 56.0 / 53.1, 66.1 / 62.6, 93.2 / 89.9; 470 MB at
-// 100 rows 97 / 89; 940 MB at 100 rows 156 / 146, at 512 (four row blocks) 404 /
-// 400; but 134 MB at 64 rows 35.1 / 38.1 and 105 MB 28.9 / 31.6.
+// most kNtRowBlocks row blocks read each weight. Weights from HBM (one call after
+// another over different weights, us, cached / non-temporal): 168 MB at 1, 16, 48, 64,
+// 128, 256 rows 33.9 / 32.5, 35.0 / 33.7, 38.4 / 38.5, 39.4 / 40.2, 46.0 / 45.5, 58.5 /
+// 57.7; 262 MB at 16, 64, 128, 256 50.8 / 47.2, 56.2 / 53.3, 64.9 / 61.2, 86.9 / 82.7; 470
+// MB at 100 95.8 / 87.3; 940 MB at 16, 512 152 / 137, 392 / 393; but 134 MB at 64 37.8 /
+// 39.7. Between layers and their activations more is gained: QKV of 168 MB at 256
+// rows 61.5 / 57.8, a 70B layer at 64 rows 350 / 345. A caller that repeats one
+// projection of up to 250 MB loses: the 256 MB memory-side cache would hold it (168 MB
+// again at 64, 256 rows 35.2 / 40.0, 48.5 / 57.6); no decode step does that.
 // And only where no row block is ragged: the workgroups of a part-filled last
 // block load fewer activations and run ahead of their pair, whose weights then
 // come from HBM again (kernel alone, us, cached / non-temporal): 470 MB at 135 rows
