@@ -83,6 +83,7 @@ struct RopeCall {
   int region;
   uint16_t* q_out;
   uint32_t* err;
+  bool beside_fill = false;  // the call runs beside a slot fill (a streamed step)
 };
 hipError_t launch_rope_append(const RopeCall& c, hipStream_t s);
 hipError_t launch_slot_mapping(const int32_t* positions, const int32_t* bt, int max_blocks, int batch, int bs,

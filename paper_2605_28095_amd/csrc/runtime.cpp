@@ -622,6 +622,7 @@ static hipError_t run_attn_half(sidp_handle* h, const uint8_t* wb, int layer, fl
   r.region = layer % h->regions;
   r.q_out = h->q;
   r.err = h->err;
+  r.beside_fill = beside_fill;
   TIMED(h, SIDP_K_ROPE, s, launch_rope_append(r, s));
   // a6: paged GQA attention
   AttnCall a;

@@ -121,6 +121,30 @@ def test_streamed_equals_resident_bitexact(lib, batch):
         st.close()
 
 
+@pytest.mark.parametrize("over", [dict(qk_norm=1), dict(qk_norm=1, qkv_bias=1, head_dim=128), dict(qkv_bias=1, batch=200),
+                                  dict(qk_norm=1, num_q_heads=16, num_kv_heads=1, head_dim=128)])
+def test_kv_append_of_streamed_steps_bitexact(lib, over):
+    """A streamed step appends with a wave per head, a resident one with several
+    heads a wave: the same queries, keys and values, hence the same bits."""
+    cfg = _small_stack_cfg(num_layers=2, num_phys_blocks=None, **over)
+    st = Stack(cfg, gains="random", regions=2, reserve=2)
+    try:
+        copy = torch.cuda.Stream()
+        outs, ran = [], []
+        for flags in (lib.SIDP_RESIDENT, lib.SIDP_STREAMED):
+            st.reset()
+            ran.append(kernels_of(lambda: st.dec.step(st.hidden, st.positions, st.bt, flags, copy=copy)))
+            st.dec.sync()
+            outs.append((st.hidden.cpu().numpy().view(np.uint32), bits(st.dec.k_cache), bits(st.dec.v_cache)))
+        for names, wave in zip(ran, (False, True)):
+            appends = [name for name in names if "k_rope_append" in name]
+            assert len(appends) == 2 and all(("k_rope_append_wave" in name) == wave for name in appends), names
+        assert np.all(np.isfinite(outs[0][0].view(np.float32)))
+        assert all(np.array_equal(a, b) for a, b in zip(*outs))
+    finally:
+        st.close()
+
+
 @pytest.mark.parametrize("batch,ctx_hi", [(8, 5000), (160, None)])
 def test_timed_steps_equal_untimed_bitexact(lib, batch, ctx_hi):
     """The timing mode the benchmark measures with changes no bits: streamed
