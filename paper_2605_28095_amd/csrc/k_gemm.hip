@@ -697,17 +697,27 @@ GemmPlan plan_linear(int m, int n, int k, int epilogue, int num_cus) {
 //  * where some CUs get two 4-wave workgroups and no row block is ragged, or the k
 //    range is short: 384 rows of 24576 x 8192 213 / 235, of a 13824 x 5120 gate/up 142
 //    / 157, 512 of 18304 x 4096 114 / 120, 300 of 24576 x 1024 39.4 / 40.4; but 300 of
-//    24576 x 4096 111 / 107, of an 11008 x 4096 gate/up 96.9 / 85.1.
+//    24576 x 4096 111 / 107, of an 11008 x 4096 gate/up 96.9 / 85.1;
+//  * where one row block of more than kAlignedRows rows has a workgroup on every CU
+//    and splits of exactly 8 or 16 k-tiles: 8192 x 8192 at 48, 64, 128 rows 34.7 / 35.8,
+//    35.8 / 37.2, 42.1 / 44.5, 8192 x 4096 at 64 25.3 / 26.2, 4096 x 8192 at 64 25.6 / 26.0;
+//    two resident 70B layers at 128 rows 821 / 832. (16384 x 4096 at 64 the other way,
+//    34.1 / 33.5; with one more k-tile, 8192 x 8256, they are level.)
 constexpr size_t kThinBytes = (size_t)150 << 20;
 constexpr int kThinRows = 24;
 constexpr int kThinTiles = 224;       // k-tiles
+constexpr int kAlignedRows = 32;
+constexpr int kAlignedTiles = 16;     // k-tiles of a split
 constexpr int kFewTiles = 32;         // k-tiles of a split times the row blocks
 constexpr int kFewTilesUnsplit = 32;  // k-tiles
 
 static bool deep_pays(const GemmArgs& a, const GemmPlan& p, int num_cus) {
   const int mblocks = (a.M + p.rows - 1) / p.rows, tiles = (a.NG + p.waves - 1) / p.waves, KT = a.KP / kBK;
   const int64_t grid = (int64_t)tiles * mblocks * p.splits;
-  if (mblocks == 1) return true;
+  if (mblocks == 1) {
+    const int each = KT / p.splits;
+    return a.M <= kAlignedRows || grid != num_cus || KT % p.splits != 0 || each % 8 != 0 || each > kAlignedTiles;
+  }
   if (a.M <= 128 + kThinRows && KT >= kThinTiles && (size_t)a.NG * 64 * a.KP * 2 >= kThinBytes) return false;
   if (p.splits > 1) return grid * 10 < 9 * (int64_t)num_cus || (int64_t)KT * mblocks > kFewTiles * (int64_t)p.splits;
   return p.waves > kWaves || grid <= num_cus || (a.M % p.rows != 0 && KT > kFewTilesUnsplit);

@@ -123,6 +123,9 @@ def _kernel(lib, m, n, k, epi):
     # few k-tiles on a full chip: 16 a split with two row blocks, 8 with four
     (200, 4096, 8192, 0, "k_gemm"), (200, 4096, 8256, 0, "k_gemm_deep"), (128, 4096, 4096, 0, "k_gemm_deep"),
     (512, 2048, 4096, 0, "k_gemm"), (512, 2048, 4160, 0, "k_gemm_deep"), (200, 12544, 1024, 0, "k_gemm_deep"),
+    # one row block on every CU, 8 or 16 k-tiles a split
+    (64, 8192, 8192, 0, "k_gemm"), (33, 8192, 4096, 0, "k_gemm"), (32, 8192, 8192, 0, "k_gemm_deep"),
+    (64, 8192, 8256, 0, "k_gemm_deep"), (64, 8192, 12288, 0, "k_gemm_deep"), (64, 10240, 8192, 0, "k_gemm_deep"),
     # two 4-wave workgroups on some CUs: 288 of them, whole row blocks or 32 k-tiles
     (384, 24576, 2112, 0, "k_gemm"), (383, 24576, 2112, 0, "k_gemm_deep"), (383, 24576, 2048, 0, "k_gemm"),
     (384, 18304, 2112, 0, "k_gemm_deep"), (512, 28672, 1024, 2, "k_gemm_deep"),
@@ -132,7 +135,8 @@ def test_the_deep_pipeline_runs_where_it_is_the_faster_one(lib, m, n, k, epi, ke
 
 
 @pytest.mark.parametrize("m,n,k,epi", [(152, 8192, 14336, 1), (200, 4096, 2056, 0), (512, 2048, 1032, 1),
-                                       (384, 24576, 328, 0), (300, 24576, 1032, 0), (257, 11008, 264, 2)])
+                                       (384, 24576, 328, 0), (300, 24576, 1032, 0), (257, 11008, 264, 2),
+                                       (100, 8192, 4096, 1)])
 def test_row_blocks_on_the_shallow_kernel(lib, m, n, k, epi):
     assert _kernel(lib, m, n, k, epi) == "k_gemm"
     _check(lib, m, n, k, epi, _x(m, k))
