@@ -46,6 +46,8 @@ constexpr float kLog2e = 1.4426950408889634f;
 // 1024-1535 26.8 / 26.4; 16 of 900-1100 23.9 / 27.2, of 1024-2040 33.0 / 30.5; 20
 // of 1800-2047 36.0 / 42.3; 24 of 1500 32.3 / 39.2, of 64-2047 31.6 / 30.2; 128
 // of 1024-2040 136.8 / 138.8; but 8 of 512-1023 20.7 / 18.1, 10 of 1500 27.2 / 22.9.
+// The host sees the table, not the lengths, so one long sequence among short ones
+// pays for it: 128 of 16-64 tokens and one of 2000 41 / 23.
 constexpr int kWholeTokens = 768;
 constexpr int kWholeTable = 2048;
 constexpr int kWholeShare = 6656;
